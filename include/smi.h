@@ -103,7 +103,11 @@ typedef struct {
 typedef enum {
     SMI_OPT_KERNEL = 0,      /* 0 (default): register-blocked half-step kernels, every shot of
                                 the batch in one launch per half step, 4 cells per lane and
-                                the XCD-contiguous order in 2D; in 3D the forward and adjoint
+                                the XCD-contiguous order in 2D, where forward passes of order 4
+                                and of sources off the grid run two steps per launch (same
+                                results; not with snapshots or
+                                SMI_OPT_TIMING, nor with receivers whose nodes span
+                                more than 16 rows); in 3D the forward and adjoint
                                 half steps of 5 (marching along y, SMI_OPT_CHUNK 432) where
                                 they apply, register-blocked kernels with 2 cells per lane
                                 elsewhere;
@@ -144,7 +148,8 @@ typedef enum {
                                 is launched with device-stamped start / stop events, and every
                                 S-th reverse iteration is bracketed by events (read with
                                 smi_kernel_timing); 0: off (default).  Setting it clears the
-                                samples collected so far.  Reverse loops are not replayed as
+                                samples collected so far.  While it is on, 2D forward passes run
+                                one step at a time (no two-step launches).  Reverse loops are not replayed as
                                 graphs while it is on. */
     SMI_OPT_TILEMAP = 4,     /* tile order of SMI_OPT_KERNEL 3 and 4: 0 plain (z-block fastest,
                                 then x-block); 1 each of the 8 XCDs takes a contiguous range of
@@ -223,7 +228,9 @@ smi_status smi_set_shot_groups(smi_ctx *ctx, int ngroup, const int *shot_off);
  * vp_min / (2.5 fm max(d)) >= ppw.  Returns SMI_OK, SMI_E_CFL, SMI_E_DISPERSION or SMI_E_ARG. */
 smi_status smi_check(const smi_ctx *ctx, const smi_grid *grid, double vp_min, double vp_max);
 
-/* Bytes of device workspace that `job` needs for this grid and acquisition. */
+/* Bytes of device workspace that `job` needs for this grid and acquisition.  (In 2D they hold a
+ * small buffer for the two-step forward launches; a call given a workspace without room for it
+ * runs the half-step kernels.) */
 smi_status smi_workspace_bytes(const smi_ctx *ctx, const smi_grid *grid, const smi_acq *acq,
                                smi_job job, size_t *bytes);
 

@@ -100,7 +100,7 @@ struct smi_ctx {
     struct Pick {
         bool fwd = false, rev = false;     // forward kernels / 2D reverse form tuned
         int march = 0, run = 32, depth = 2, rev_form = 0, yp = 0, y3 = 0;
-        bool xcd = false, ymap = false, step2d = false;
+        bool xcd = false, ymap = false, step2d = false, steps = false;
     };
     std::map<std::string, Pick> picks;
     struct RevTune {
@@ -153,6 +153,7 @@ void apply_pick(smi::StepCtx &c, const smi_ctx *ctx, const Plan &pl, bool forwar
         c.xcd = p.xcd;
         c.ymap = p.ymap;
         c.step2d = p.step2d;
+        c.steps = p.steps;
         c.run = p.run;
         c.depth = p.depth;
         c.yp = p.yp;
@@ -176,6 +177,7 @@ void configure(smi::StepCtx &c, const smi_ctx *ctx, const Plan &pl) {
     c.ymap = false;
     c.rev = ctx->opt_rev;
     c.step2d = false;
+    c.steps = false;
     c.run = 32;
     c.depth = 2;
     c.yp = 0;
@@ -215,6 +217,7 @@ void configure(smi::StepCtx &c, const smi_ctx *ctx, const Plan &pl) {
     } else if (ctx->opt_kernel == 0) {
         c.march = pl.nd == 2 ? 4 : 2;
         c.xcd = pl.nd == 2;
+        c.steps = smi::steps2d_default(pl);
     } else if (ctx->opt_kernel == 2) {
         c.march = ctx->opt_chunk % 100 == 8 ? 8 : 4;
         c.zl = ctx->opt_chunk >= 100;   // the tiled variant of the fused step
@@ -277,10 +280,10 @@ Key plan_key(char tag, const Plan &pl, const smi::StepCtx &c) {
     Key k;
     k.put(tag).put(pl.geom).put(pl.band).put(pl.nshot).put(pl.nrun).put(pl.nsave);
     k.put(pl.save).put(pl.g.nt).put(pl.g.dr).put(c.plain).put(c.march).put(c.xcd).put(c.zl).put(c.rev).put(c.ymap);
-    k.put(c.y3).put(pl.chunk).put(c.step2d).put(c.run).put(c.depth).put(c.yp);
+    k.put(c.y3).put(pl.chunk).put(c.steps).put(c.step2d).put(c.run).put(c.depth).put(c.yp);
     k.vec(pl.fbox).vec(pl.abox).vec(pl.rbox).vec(pl.rec_off);
     k.put(pl.src_multi).vec(pl.src_toff).vec(pl.src_cell).vec(pl.inj_off);
-    k.put(pl.inj_fused).put(pl.inj_zlo).put(pl.inj_nrow);
+    k.put(pl.inj_fused).put(pl.inj_zlo).put(pl.inj_nrow).put(pl.rec_zlo).put(pl.rec_nrow);
     return k;
 }
 
@@ -407,13 +410,9 @@ smi_status upload(smi_ctx *ctx, const Plan &pl, const Views &w, hipStream_t st) 
     return SMI_OK;
 }
 
-size_t field_bytes(const Plan &pl) {
-    return sizeof(float) * (size_t)pl.nshot * ((size_t)pl.P * (1 + pl.nd) +
-           2 * (size_t)(pl.geom.psz[0] + pl.geom.psz[1] + pl.geom.psz[2]));
-}
 
 smi_status zero_fields(smi_ctx *ctx, const Plan &pl, const smi::Fields &f, hipStream_t st) {
-    HIPCHK(hipMemsetAsync(f.p, 0, field_bytes(pl), st), "field clear");
+    HIPCHK(hipMemsetAsync(f.p, 0, fields_bytes(pl), st), "field clear");
     return SMI_OK;
 }
 
@@ -451,6 +450,7 @@ struct Cand {
     int run, depth;
     const char *name;
     int yp = 0, y3 = 0;
+    bool steps = false;
 };
 
 std::vector<Cand> fwd_candidates(const Plan &pl) {
@@ -460,6 +460,7 @@ std::vector<Cand> fwd_candidates(const Plan &pl) {
         v.push_back({2, true, false, false, 32, 2, "march2-xcd"});
         v.push_back({8, true, false, false, 32, 2, "march8-xcd"});
         v.push_back({4, false, false, false, 32, 2, "march4-plain"});
+        if (smi::steps2d_available(pl)) v.push_back({4, true, false, false, 32, 2, "two-steps", 0, 0, true});
         if (smi::step2d_available(pl)) {
             v.push_back({4, true, false, true, 32, 2, "fused-c32-d2"});
             v.push_back({4, true, false, true, 64, 2, "fused-c64-d2"});
@@ -485,6 +486,7 @@ void set_cand(smi::StepCtx &c, const Cand &q) {
     c.xcd = q.xcd;
     c.ymap = q.ymap;
     c.step2d = q.step2d;
+    c.steps = q.steps;
     c.run = q.run;
     c.depth = q.depth;
     c.yp = q.yp;
@@ -522,8 +524,10 @@ smi_status tune_forward(smi_ctx *ctx, const Plan &pl, const Views &w, smi::StepC
     for (size_t q = 0; q < cands.size(); ++q) {
         set_cand(t, cands[q]);
         HIPCHK(hipEventRecord(ctx->tune_events[2 * q], st), "tuning event");
+        for (size_t k = 0; t.steps && k + smi::kSteps <= steps.size(); k += smi::kSteps)
+            HIPCHK(smi::fwd_steps_2d(t, w.f, w.f2, steps[k], 0), "tuning step");
         for (int it : steps)
-            HIPCHK(t.step2d ? smi::fwd_step_2d(t, w.f, w.f2, it) : smi::fwd_step(t, it), "tuning step");
+            if (!t.steps) HIPCHK(t.step2d ? smi::fwd_step_2d(t, w.f, w.f2, it) : smi::fwd_step(t, it), "tuning step");
         HIPCHK(hipEventRecord(ctx->tune_events[2 * q + 1], st), "tuning event");
     }
     HIPCHK(hipEventSynchronize(ctx->tune_events[2 * cands.size() - 1]), "tuning sync");
@@ -545,6 +549,7 @@ smi_status tune_forward(smi_ctx *ctx, const Plan &pl, const Views &w, smi::StepC
     p.xcd = cands[best].xcd;
     p.ymap = cands[best].ymap;
     p.step2d = cands[best].step2d;
+    p.steps = cands[best].steps;
     p.run = cands[best].run;
     p.depth = cands[best].depth;
     p.yp = cands[best].yp;
@@ -608,12 +613,21 @@ smi_status run_forward(smi_ctx *ctx, const Plan &pl, const Views &w, const float
     }
     for (int k = 0; k < nsnap; ++k)
         if (snap_it[k] == 0) HIPCHK(smi::snap(c, w.f, snaps, k, nsnap), "snap");
+    // snapshots may fall between the levels of a two-step launch, and timing is of half steps
+    if (nsnap > 0 || ctx->opt_timing > 0) c.steps = false;
     const bool f2d = c.step2d;
     bool fused = f2d || (ctx->opt_kernel == 2 && pl.dbuf && pl.g.dr == 1 && smi::fused_fwd_available(pl));
-    if (fused) {
+    if (fused || c.steps) {
         s = zero_fields(ctx, pl, w.f2, st);
         if (s != SMI_OK) return s;
     }
+    // the pipelined step keeps the receiver rows and saves the band cells inside the computing boxes; the others are at rest
+    if (c.steps && pl.save)
+        HIPCHK(hipMemsetAsync(w.bands, 0, sizeof(float) * (size_t)pl.nshot * pl.nsave * pl.band.B, st),
+               "band clear");
+    if (c.steps)
+        HIPCHK(hipMemsetAsync(w.side, 0, smi::side_bytes(pl), st),
+               "receiver rows clear");
     const int nt = pl.g.nt, dr = pl.g.dr;
     const bool timed = ctx->opt_timing > 0 && !c.plain;
     const bool defer = !fused && smi::march_forward(c);
@@ -643,7 +657,33 @@ smi_status run_forward(smi_ctx *ctx, const Plan &pl, const Views &w, const float
         c.s0 = fg[gi];
         c.s1 = fg[gi + 1];
         c.ext_it = -1;
+        int pend = -1, par = 0;     // the launch of pipelined steps whose receivers are still to be sampled
         for (int it = 0; it < pl.nrun; ++it) {
+            // pipelined steps: an even number of launches up to level nt (and past it, to the last
+            // saved level), so that each stretch ends in the first buffer; the steps left over run
+            // first, one at a time
+            const int end = it < nt ? nt : pl.nrun;
+            if (c.steps && (end - it) % (2 * smi::kSteps) == 0) {
+                if (c.ext_it >= 0) {
+                    HIPCHK(smi::extract(c, c.ext_it, dcal), "extract");
+                    c.ext_it = -1;
+                }
+                if (pl.save && it % dr == 0) HIPCHK(smi::band_save(c, w.f, it / dr), "band save");
+                for (; it < end; it += smi::kSteps) {
+                    const bool odd = par & 1;
+                    c.ext_it = pend;
+                    c.ext_dcal = dcal;
+                    HIPCHK(smi::fwd_steps_2d(c, odd ? w.f2 : w.f, odd ? w.f : w.f2, it, par & 1), "forward steps");
+                    c.ext_it = -1;
+                    pend = it < nt ? it : -1;
+                    ++par;
+                }
+                if (pend >= 0) HIPCHK(smi::steps2d_extract(c, pend, (par ^ 1) & 1, dcal), "extract");
+                pend = -1;
+                if (w.fin && end == nt) HIPCHK(copy_state(w.fin, w.f.p, ls), "final copy");
+                --it;
+                continue;
+            }
             // fused steps alternate between the two buffers: level it lives in cur
             const smi::Fields &cur = fused && (it & 1) ? w.f2 : w.f;
             const smi::Fields &nxt = fused && !(it & 1) ? w.f2 : w.f;
@@ -715,7 +755,7 @@ smi_status run_forward(smi_ctx *ctx, const Plan &pl, const Views &w, const float
         }
         if (fused && (pl.nrun & 1)) {
             // the final level is in the second buffer; the reverse pass works on the first
-            HIPCHK(hipMemcpyAsync(w.f.p, w.f2.p, field_bytes(pl), hipMemcpyDeviceToDevice, ls),
+            HIPCHK(hipMemcpyAsync(w.f.p, w.f2.p, fields_bytes(pl), hipMemcpyDeviceToDevice, ls),
                    "final state copy");
         }
         if (pl.save && dr > 1) {
@@ -909,6 +949,8 @@ smi_status forward_common(smi_ctx *ctx, const smi_grid *grid, const smi_acq *acq
         snprintf(b, sizeof b, "workspace has %zu bytes, %zu needed", ws_bytes, stt->plan.bytes);
         return fail(ctx, SMI_E_WORKSPACE, b);
     }
+    // (a workspace without room for the receiver rows of the pipelined step runs the other kernels)
+    if (stt->plan.side && ws_bytes < stt->plan.bytes_full) smi::layout(stt->plan, false);
     stt->plan.chunk = ctx->opt_chunk;
     Views w = smi::views(stt->plan, ws);
     s = run_forward(ctx, stt->plan, w, vp, rho, stf, dcal, snap_it, nsnap, snaps, st);
@@ -999,10 +1041,15 @@ smi_status smi_check(const smi_ctx *ctx, const smi_grid *grid, double vp_min, do
     return s;
 }
 
-smi_status smi_workspace_bytes(const smi_ctx *ctx, const smi_grid *grid, const smi_acq *acq,
-                               smi_job job, size_t *bytes) {
+}  // extern "C"
+
+namespace {
+
+// Workspace of a job: the least it runs with, and what every kernel of its default has room in.
+smi_status workspace_need(const smi_ctx *ctx, const smi_grid *grid, const smi_acq *acq, smi_job job,
+                          size_t *least, size_t *full) {
     smi_ctx *c = const_cast<smi_ctx *>(ctx);
-    if (!grid || !acq || !bytes) return fail(c, SMI_E_ARG, "NULL argument");
+    if (!grid || !acq) return fail(c, SMI_E_ARG, "NULL argument");
     if (job < SMI_JOB_FORWARD || job > SMI_JOB_BORN) return fail(c, SMI_E_ARG, "bad job");
     // the layout does not depend on the speeds; use a range that passes the checks
     smi_grid g = *grid;
@@ -1017,8 +1064,20 @@ smi_status smi_workspace_bytes(const smi_ctx *ctx, const smi_grid *grid, const s
     smi_status s = smi::make_plan(&g, acq, job, vmin, vmax, pl, err);
     if (c) c->err = err;
     if (s != SMI_OK) return s;
-    *bytes = pl.bytes;
+    *least = pl.bytes;
+    *full = pl.bytes_full;
     return SMI_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+smi_status smi_workspace_bytes(const smi_ctx *ctx, const smi_grid *grid, const smi_acq *acq,
+                               smi_job job, size_t *bytes) {
+    if (!bytes) return fail(const_cast<smi_ctx *>(ctx), SMI_E_ARG, "NULL argument");
+    size_t least = 0;
+    return workspace_need(ctx, grid, acq, job, &least, bytes);
 }
 
 smi_status smi_forward(smi_ctx *ctx, const smi_grid *grid, const smi_acq *acq, const float *vp,
@@ -1043,8 +1102,8 @@ smi_status smi_forward_static(smi_ctx *ctx, const smi_grid *grid, const smi_acq 
     void *ws = scratch_of(ctx->device);
     if (!ws || !ctx->scratch_err.empty())
         return fail(ctx, SMI_E_HIP, ctx->scratch_err.empty() ? "static workspace unavailable" : ctx->scratch_err);
-    size_t need = 0;
-    smi_status s = smi_workspace_bytes(ctx, grid, acq, SMI_JOB_FORWARD, &need);
+    size_t need = 0, full = 0;
+    smi_status s = workspace_need(ctx, grid, acq, SMI_JOB_FORWARD, &need, &full);
     if (s != SMI_OK) return s;
     if (need > (size_t)SMI_STATIC_WS_BYTES) {
         char b[200];

@@ -610,13 +610,35 @@ smi_status make_plan(const smi_grid *g, const smi_acq *acq, smi_job job, double 
         }
     }
 
+    pl.npartial = std::max(1024, acq->nshot);   // also holds the per-shot peak illumination
+    // rows of the receivers' nodes, which the pipelined 2D forward step keeps
+    if (pl.nd == 2 && !pl.born) {
+        int lo = 1 << 30, hi = -1;
+        for (long long cell : pl.rec_tcell) {
+            const int z = (int)((cell - pl.org) % pl.ld1);
+            lo = std::min(lo, z);
+            hi = std::max(hi, z);
+        }
+        pl.rec_zlo = hi < 0 ? 0 : lo;
+        pl.rec_nrow = hi < 0 ? 1 : hi - lo + 1;
+    }
+    pl.bytes = layout(pl, false);
+    pl.bytes_full = pl.rec_nrow > 0 && pl.rec_nrow <= kSideRows ? layout(pl, true) : pl.bytes;
+    return SMI_OK;
+}
+
+size_t layout(Plan &pl, bool side) {
+    const Geom &G = pl.geom;
+    const smi_grid *g = &pl.g;
+    const BandDesc &bd = pl.band;
+    const int ns = pl.nshot, nt = pl.g.nt, R = pl.rec_off[pl.nshot];
+    pl.side = side;
     // workspace layout
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t r = o; o = align_up(o + bytes, 256); return r; };
     pl.off_status = take(64);
     pl.off_misfit = take(16);
     pl.off_bdesc = take(sizeof(BandDesc));
-    pl.npartial = std::max(1024, acq->nshot);   // also holds the per-shot peak illumination
     pl.off_partial = take(sizeof(double) * pl.npartial);
     pl.off_model = take(sizeof(float) * (size_t)pl.P * (1 + pl.nd));
     size_t cp = 0;
@@ -635,6 +657,7 @@ smi_status make_plan(const smi_grid *g, const smi_acq *acq, smi_job job, double 
     pl.off_fields = take(fld);
     pl.dbuf = pl.nd == 2;
     pl.off_fields2 = pl.dbuf ? take(fld) : 0;
+    pl.off_side = side ? take(side_bytes(pl)) : 0;
     pl.off_adj = pl.adjoint || pl.born ? take(fld) : 0;
     pl.off_bands = pl.save ? take(sizeof(float) * (size_t)ns * pl.nsave * (size_t)bd.B) : 0;
     pl.off_fin = pl.save && g->dr > 1 ? take(sizeof(float) * (size_t)ns * (size_t)pl.P * (1 + pl.nd)) : 0;
@@ -645,8 +668,7 @@ smi_status make_plan(const smi_grid *g, const smi_acq *acq, smi_job job, double 
     // tail slack: the fused 2D step reads (and never uses) up to kTailCols columns of a
     // field or model array past the ghost frame of the last shot
     take(sizeof(float) * (size_t)kTailCols * pl.ld1);
-    pl.bytes = o;
-    return SMI_OK;
+    return o;
 }
 
 Views views(const Plan &pl, void *ws) {
@@ -741,6 +763,7 @@ Views views(const Plan &pl, void *ws) {
     w.G = pl.need_G ? (float *)(b + pl.off_G) : nullptr;
     w.dcal = pl.need_dcal ? (float *)(b + pl.off_dcal) : nullptr;
     w.fin = pl.off_fin ? (float *)(b + pl.off_fin) : nullptr;
+    w.side = pl.side ? (float *)(b + pl.off_side) : nullptr;
     return w;
 }
 

@@ -28,6 +28,9 @@ constexpr int kTaps = 4;       // half-width (saved levels) of the decimated-ban
 constexpr int kTailCols = 32;  // columns of workspace slack after the last region (see plan.cpp)
 constexpr size_t kInjMapCap = size_t(1) << 22;   // entries of the largest adjoint-source node map
 constexpr double kKaiserBeta = 6.31;
+constexpr int kSteps = 2;      // time steps per launch of the pipelined 2D forward step (steps2d.hip)
+constexpr int kSideRows = 16;  // most rows of p kept per level for receivers between its launches
+constexpr int kSidePad = 8;    // columns of room after them
 
 // ---------------------------------------------------------------- device-side views
 
@@ -154,7 +157,13 @@ struct Plan {
     size_t off_fields = 0, off_fields2 = 0, off_adj = 0, off_bands = 0, off_acc = 0, off_G = 0, off_dcal = 0;
     size_t off_rho = 0;
     size_t off_taps = 0, off_fin = 0, off_inj = 0, off_injmap = 0;
-    size_t bytes = 0;
+    // pipelined 2D forward step: rows [rec_zlo, rec_zlo + rec_nrow) hold every receiver's nodes; a
+    // launch keeps them per level in the side rows, after the fields.  A workspace of `bytes`
+    // without them is enough for the other kernels; bytes_full has room for them
+    int rec_zlo = 0, rec_nrow = 0;
+    size_t off_side = 0;
+    bool side = false;             // the layout holds the side rows
+    size_t bytes = 0, bytes_full = 0;
     int npartial = 0;
     bool save = false, adjoint = false, need_G = false, need_dcal = false;
     bool rho_acc = false;   // room for the density-gradient face sums (gradient-capable jobs)
@@ -176,6 +185,8 @@ struct Plan {
 // Build and validate a plan.  Returns SMI_OK or an error with `err` filled.
 smi_status make_plan(const smi_grid *g, const smi_acq *acq, smi_job job, double vmin,
                      double vmax, Plan &pl, std::string &err);
+// lay the workspace out, with the side rows of the pipelined 2D step or without; its size
+size_t layout(Plan &pl, bool side);
 smi_status check_grid(const smi_grid *g, double vmin, double vmax, std::string &err);
 void algorithmic_bytes(Plan &pl);
 // algorithmic bytes of forward step it over the shots [s0, s1), as a row of Plan::step_bytes
@@ -222,9 +233,20 @@ struct Views {
     float *G;           // [nt * R] adjoint source (when computed internally)
     float *dcal;        // internal dcal when the caller gave none
     float *fin;         // level-nt copy of p and v while the forward runs past nt (dr > 1)
+    float *side;        // [2][kSteps][nshot][M[1] + kSidePad][rec_nrow] receiver rows of two launches
 };
 
 Views views(const Plan &pl, void *ws);
+
+// bytes of the receiver rows of the pipelined 2D step (two launches)
+inline size_t side_bytes(const Plan &pl) {
+    return sizeof(float) * 2 * kSteps * (size_t)pl.nshot * pl.rec_nrow * (pl.M[1] + kSidePad);
+}
+// bytes of one field set (p, v and the memory variables of every shot)
+inline size_t fields_bytes(const Plan &pl) {
+    return sizeof(float) * (size_t)pl.nshot * ((size_t)pl.P * (1 + pl.nd) +
+           2 * (size_t)(pl.geom.psz[0] + pl.geom.psz[1] + pl.geom.psz[2]));
+}
 
 // ---------------------------------------------------------------- launchers (kernels.hip)
 
@@ -247,6 +269,7 @@ struct StepCtx {
     bool zl = false;        // register-blocked kernels take z-neighbours from LDS
     int y3 = 0;             // 3D: half steps marching along y, tile code 100 BX + CY (0: off)
     int yp = 0;             // 3D: plane-tiled half steps marching along y, CY planes (0: off)
+    bool steps = false;     // 2D forward: kSteps time steps per launch (steps2d.hip)
     int rev = 0;            // 2D reverse step: 0 by batch size, 1 two launches, 2 five launches
     bool step2d = false;    // 2D forward: the fused marching step (step2d.hip), levels in two buffers
     int run = 32;           // its run of columns per wavefront or tile (32 or 64)
@@ -289,6 +312,14 @@ hipError_t fwd_step_fused(const StepCtx &c, const Fields &src, const Fields &dst
 // c.save_p_slot >= 0, the bands of level it (from src) on extra workgroups
 bool step2d_available(const Plan &pl);
 hipError_t fwd_step_2d(const StepCtx &c, const Fields &src, const Fields &dst, int it);
+// kSteps forward steps from it on, from src into dst, every shot of the context in one launch;
+// carries the receivers of the previous launch's levels (first step c.ext_it) and saves the bands
+// of its own levels.  par alternates between consecutive launches (the half of the side rows).
+bool steps2d_available(const Plan &pl);
+bool steps2d_default(const Plan &pl);   // where it is the default
+hipError_t fwd_steps_2d(const StepCtx &c, const Fields &src, const Fields &dst, int it, int par);
+// the receivers of a launch (first step it, side half par) when no launch follows it
+hipError_t steps2d_extract(const StepCtx &c, int it, int par, float *dcal);
 hipError_t extract(const StepCtx &c, int it, float *dcal, const float *p = nullptr);
 // p += sign dt stf[it] / dV through the operators of the sources that spread over several
 // nodes (one-tap sources are injected inside the p kernels); nothing when there are none
