@@ -933,8 +933,11 @@ smi_status forward_common(smi_ctx *ctx, const smi_grid *grid, const smi_acq *acq
                           smi_job job, const float *vp, const float *rho, const float *stf,
                           float *dcal, const int *snap_it, int nsnap, float *snaps, void *ws,
                           size_t ws_bytes, hipStream_t st, std::unique_ptr<smi_state> &out) {
+    // (RTM and gradient jobs without a caller's dcal record into the workspace's own)
     if (!grid || !acq) return fail(ctx, SMI_E_ARG, "grid / acq is NULL");
-    if (!vp || !rho || !stf || !dcal) return fail(ctx, SMI_E_ARG, "vp, rho, stf and dcal are required");
+    const bool own = job == SMI_JOB_RTM || job == SMI_JOB_GRAD;
+    if (!vp || !rho || !stf || (!dcal && !own))
+        return fail(ctx, SMI_E_ARG, "vp, rho, stf and dcal are required");
     if (!ws) return fail(ctx, SMI_E_WORKSPACE, "workspace is NULL");
     smi_status s = check_snaps(ctx, grid, snap_it, nsnap, snaps);
     if (s != SMI_OK) return s;
@@ -953,6 +956,7 @@ smi_status forward_common(smi_ctx *ctx, const smi_grid *grid, const smi_acq *acq
     if (stt->plan.side && ws_bytes < stt->plan.bytes_full) smi::layout(stt->plan, false);
     stt->plan.chunk = ctx->opt_chunk;
     Views w = smi::views(stt->plan, ws);
+    if (!dcal) dcal = w.dcal;
     s = run_forward(ctx, stt->plan, w, vp, rho, stf, dcal, snap_it, nsnap, snaps, st);
     if (s != SMI_OK) return s;
     stt->ctx = ctx;
@@ -1061,7 +1065,7 @@ smi_status workspace_need(const smi_ctx *ctx, const smi_grid *grid, const smi_ac
         vmin = vmax;
         g.fm = 1e-9;          // no dispersion limit
     }
-    smi_status s = smi::make_plan(&g, acq, job, vmin, vmax, pl, err);
+    smi_status s = smi::make_plan(&g, acq, job, vmin, vmax, pl, err, true);
     if (c) c->err = err;
     if (s != SMI_OK) return s;
     *least = pl.bytes;
@@ -1151,25 +1155,14 @@ smi_status smi_rtm_image(smi_ctx *ctx, const smi_grid *grid, const smi_acq *acq,
     if (!ctx) return SMI_E_ARG;
     if (!dobs) return fail(ctx, SMI_E_ARG, "dobs is NULL");
     hipStream_t st = (hipStream_t)hip_stream;
-    // the internal dcal buffer sits inside ws; plan once to find it
-    double vmin = 0, vmax = 0;
-    smi_status s = speeds(ctx, grid, vp, ws, ws_bytes, st, vmin, vmax);
-    if (s != SMI_OK) return s;
-    smi_grid g = *grid;
-    g.vpmin = vmin;
-    g.vpmax = vmax;
-    Plan pl;
-    s = smi::make_plan(&g, acq, SMI_JOB_RTM, vmin, vmax, pl, ctx->err);
-    if (s != SMI_OK) return s;
-    if (!ws || ws_bytes < pl.bytes) return fail(ctx, SMI_E_WORKSPACE, "workspace too small");
-    Views w = smi::views(pl, ws);
     std::unique_ptr<smi_state> stt;
-    s = forward_common(ctx, &g, acq, SMI_JOB_RTM, vp, rho, stf, w.dcal, nullptr, 0, nullptr, ws,
-                       ws_bytes, st, stt);
+    smi_status s = forward_common(ctx, grid, acq, SMI_JOB_RTM, vp, rho, stf, nullptr, nullptr, 0,
+                                  nullptr, ws, ws_bytes, st, stt);
     if (s != SMI_OK) return s;
+    const Views w = smi::views(stt->plan, ws);
     smi::StepCtx c{&stt->plan, &w, stf, st, false};
     configure(c, ctx, stt->plan);
-    HIPCHK(smi::scale_copy(c, dobs, w.G, (float)g.dt), "rtm source");
+    HIPCHK(smi::scale_copy(c, dobs, w.G, (float)grid->dt), "rtm source");
     return run_reverse(ctx, stt.get(), w.G, nullptr, nullptr, image, illum, image_norm, nullptr, 0,
                        nullptr, st);
 }
@@ -1182,22 +1175,12 @@ smi_status smi_fwi_grad(smi_ctx *ctx, const smi_grid *grid, const smi_acq *acq, 
     if (!dobs || (!grad_vp && !grad_rho))
         return fail(ctx, SMI_E_ARG, "dobs and at least one of grad_vp, grad_rho are required");
     hipStream_t st = (hipStream_t)hip_stream;
-    double vmin = 0, vmax = 0;
-    smi_status s = speeds(ctx, grid, vp, ws, ws_bytes, st, vmin, vmax);
-    if (s != SMI_OK) return s;
-    smi_grid g = *grid;
-    g.vpmin = vmin;
-    g.vpmax = vmax;
-    Plan pl;
-    s = smi::make_plan(&g, acq, SMI_JOB_GRAD, vmin, vmax, pl, ctx->err);
-    if (s != SMI_OK) return s;
-    if (!ws || ws_bytes < pl.bytes) return fail(ctx, SMI_E_WORKSPACE, "workspace too small");
-    Views w = smi::views(pl, ws);
-    float *dcal = dcal_out ? dcal_out : w.dcal;
     std::unique_ptr<smi_state> stt;
-    s = forward_common(ctx, &g, acq, SMI_JOB_GRAD, vp, rho, stf, dcal, nullptr, 0, nullptr, ws,
-                       ws_bytes, st, stt);
+    smi_status s = forward_common(ctx, grid, acq, SMI_JOB_GRAD, vp, rho, stf, dcal_out, nullptr, 0,
+                                  nullptr, ws, ws_bytes, st, stt);
     if (s != SMI_OK) return s;
+    const Views w = smi::views(stt->plan, ws);
+    const float *dcal = dcal_out ? dcal_out : w.dcal;
     smi::StepCtx c{&stt->plan, &w, stf, st, false};
     configure(c, ctx, stt->plan);
     std::vector<int> grp;

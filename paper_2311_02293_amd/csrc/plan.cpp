@@ -158,20 +158,40 @@ static bool axis_taps(double pos, double h, int n, int nb, int M, int r, int &ne
 }
 
 // Tensor-product operator of one point: appends its taps; `node` receives the nearest node.
+// `last` keeps the operators along the axes from one point to the next of a loop (a spread has one
+// depth, and a line of a grid one coordinate).
+struct AxisTaps {
+    double pos = 0;
+    bool set = false;
+    int node = 0;
+    std::vector<int> nd;
+    std::vector<double> w;
+};
+
 static bool point_taps(const Plan &pl, const double *pos, const double *hs, int *node,
-                       std::vector<long long> &cell, std::vector<float> &wt) {
-    std::vector<int> nd[3];
-    std::vector<double> ww[3];
+                       std::vector<long long> &cell, std::vector<float> &wt, AxisTaps *last) {
     for (int a = 0; a < 3; ++a) {
-        if (a >= pl.nd) { nd[a] = {0}; ww[a] = {1.0}; node[a] = 0; continue; }
-        if (!axis_taps(pos[a], hs[a], pl.n[a], pl.g.nb, pl.M[a], pl.N, node[a], nd[a], ww[a]))
-            return false;
+        AxisTaps &t = last[a];
+        if (a >= pl.nd) {
+            t.nd = {0};
+            t.w = {1.0};
+            node[a] = 0;
+            continue;
+        }
+        if (!t.set || t.pos != pos[a]) {
+            t.set = axis_taps(pos[a], hs[a], pl.n[a], pl.g.nb, pl.M[a], pl.N, t.node, t.nd, t.w);
+            t.pos = pos[a];
+            if (!t.set) return false;
+        }
+        node[a] = t.node;
     }
-    for (size_t k = 0; k < nd[2].size(); ++k)
-        for (size_t j = 0; j < nd[1].size(); ++j)
-            for (size_t i = 0; i < nd[0].size(); ++i) {
-                cell.push_back(pl.cell(nd[0][i], nd[1][j], nd[2][k]));
-                wt.push_back((float)(ww[0][i] * ww[1][j] * ww[2][k]));
+    const std::vector<int> *nd[3] = {&last[0].nd, &last[1].nd, &last[2].nd};
+    const std::vector<double> *ww[3] = {&last[0].w, &last[1].w, &last[2].w};
+    for (size_t k = 0; k < nd[2]->size(); ++k)
+        for (size_t j = 0; j < nd[1]->size(); ++j)
+            for (size_t i = 0; i < nd[0]->size(); ++i) {
+                cell.push_back(pl.cell((*nd[0])[i], (*nd[1])[j], (*nd[2])[k]));
+                wt.push_back((float)((*ww[0])[i] * (*ww[1])[j] * (*ww[2])[k]));
             }
     return true;
 }
@@ -356,7 +376,7 @@ std::vector<int> rev_groups(const Plan &pl, double budget, int max_per, bool rho
 }
 
 smi_status make_plan(const smi_grid *g, const smi_acq *acq, smi_job job, double vmin,
-                     double vmax, Plan &pl, std::string &err) {
+                     double vmax, Plan &pl, std::string &err, bool sizes) {
     smi_status st = check_grid(g, vmin, vmax, err);
     if (st != SMI_OK) return st;
     if (!acq || acq->nshot < 1 || !acq->src || !acq->rec_off) {
@@ -395,8 +415,9 @@ smi_status make_plan(const smi_grid *g, const smi_acq *acq, smi_job job, double 
     pl.src_tcell.clear();
     pl.src_tw.clear();
     pl.src_multi = false;
+    AxisTaps last[3];
     for (int s = 0; s < pl.nshot; ++s) {
-        if (!point_taps(pl, &acq->src[3 * s], hs, &pl.src[3 * s], pl.src_tcell, pl.src_tw)) {
+        if (!point_taps(pl, &acq->src[3 * s], hs, &pl.src[3 * s], pl.src_tcell, pl.src_tw, last)) {
             err = "source " + std::to_string(s) + " lies outside the model";
             return SMI_E_ARG;
         }
@@ -409,13 +430,32 @@ smi_status make_plan(const smi_grid *g, const smi_acq *acq, smi_job job, double 
     pl.rec_toff.assign(1, 0);
     pl.rec_tcell.clear();
     pl.rec_tw.clear();
-    for (int r = 0; r < R; ++r) {
-        if (!point_taps(pl, &acq->rec[3 * (size_t)r], hs, &pl.rec[3 * (size_t)r], pl.rec_tcell,
-                        pl.rec_tw)) {
-            err = "receiver " + std::to_string(r) + " lies outside the model";
-            return SMI_E_ARG;
+    // a shot with the receiver positions of the shot before takes over its operators (surveys have
+    // one spread for many shots)
+    std::vector<char> same(pl.nshot, 0);
+    for (int s = 0; s < pl.nshot; ++s) {
+        const int r0 = pl.rec_off[s], nr = pl.rec_off[s + 1] - r0;
+        const int q0 = s ? pl.rec_off[s - 1] : 0;
+        same[s] = s && nr > 0 && r0 - q0 == nr &&
+                  std::memcmp(acq->rec + 3 * (size_t)r0, acq->rec + 3 * (size_t)q0, 3 * sizeof(double) * nr) == 0;
+        if (same[s]) {
+            const int t0 = pl.rec_toff[q0], t1 = pl.rec_toff[r0];
+            pl.rec_tcell.resize(pl.rec_tcell.size() + (t1 - t0));
+            pl.rec_tw.resize(pl.rec_tw.size() + (t1 - t0));
+            std::copy(&pl.rec_tcell[t0], &pl.rec_tcell[t0] + (t1 - t0), &pl.rec_tcell[t1]);
+            std::copy(&pl.rec_tw[t0], &pl.rec_tw[t0] + (t1 - t0), &pl.rec_tw[t1]);
+            std::copy(&pl.rec[3 * (size_t)q0], &pl.rec[3 * (size_t)q0] + 3 * (size_t)nr, &pl.rec[3 * (size_t)r0]);
+            for (int r = 0; r < nr; ++r) pl.rec_toff.push_back(pl.rec_toff[q0 + r + 1] + (t1 - t0));
+            continue;
         }
-        pl.rec_toff.push_back((int)pl.rec_tcell.size());
+        for (int r = r0; r < r0 + nr; ++r) {
+            if (!point_taps(pl, &acq->rec[3 * (size_t)r], hs, &pl.rec[3 * (size_t)r], pl.rec_tcell,
+                            pl.rec_tw, last)) {
+                err = "receiver " + std::to_string(r) + " lies outside the model";
+                return SMI_E_ARG;
+            }
+            pl.rec_toff.push_back((int)pl.rec_tcell.size());
+        }
     }
     // gather form of the adjoint-source injection: per shot, the distinct nodes of its
     // receivers' operators in ascending cell order, each with its (receiver, weight) pairs in
@@ -425,10 +465,37 @@ smi_status make_plan(const smi_grid *g, const smi_acq *acq, smi_job job, double 
     pl.inj_rec.clear();
     pl.inj_w.clear();
     pl.inj_off.assign(1, 0);
+    std::vector<std::pair<long long, int>> ct;       // (cell, tap index), taps in receiver order
+    std::vector<int> rec_of;                         // receiver of a tap, within its shot
+    size_t prev_u = 0, prev_t = 0;                   // where the gather of the shot before starts
     for (int s = 0; s < pl.nshot; ++s) {
-        std::vector<std::pair<long long, int>> ct;   // (cell, tap index), taps in receiver order
+        const size_t u0 = pl.inj_cell.size(), e0 = pl.inj_rec.size();
+        if (same[s]) {
+            // the same nodes and contributions, of this shot's receivers
+            const int dr = pl.rec_off[s] - pl.rec_off[s - 1];
+            const int dt = (int)(e0 - prev_t);
+            for (size_t u = prev_u; u < u0; ++u) {
+                pl.inj_shot.push_back(s);
+                pl.inj_cell.push_back(pl.inj_cell[u]);
+                pl.inj_off.push_back(pl.inj_off[u + 1] + dt);
+            }
+            for (size_t e = prev_t; e < e0; ++e) {
+                pl.inj_rec.push_back(pl.inj_rec[e] + dr);
+                pl.inj_w.push_back(pl.inj_w[e]);
+            }
+            prev_u = u0;
+            prev_t = e0;
+            continue;
+        }
+        prev_u = u0;
+        prev_t = e0;
+        ct.clear();
+        rec_of.clear();
         for (int r = pl.rec_off[s]; r < pl.rec_off[s + 1]; ++r)
-            for (int t = pl.rec_toff[r]; t < pl.rec_toff[r + 1]; ++t) ct.emplace_back(pl.rec_tcell[t], t);
+            for (int t = pl.rec_toff[r]; t < pl.rec_toff[r + 1]; ++t) {
+                ct.emplace_back(pl.rec_tcell[t], t);
+                rec_of.push_back(r);
+            }
         std::stable_sort(ct.begin(), ct.end(),
                          [](const std::pair<long long, int> &a, const std::pair<long long, int> &b) {
                              return a.first < b.first;
@@ -440,10 +507,7 @@ smi_status make_plan(const smi_grid *g, const smi_acq *acq, smi_job job, double 
                 pl.inj_cell.push_back(ct[i].first);
             }
             const int t = ct[i].second;
-            // receiver of tap t: taps of receiver r are rec_toff[r] .. rec_toff[r+1)
-            const int r = (int)(std::upper_bound(pl.rec_toff.begin(), pl.rec_toff.end(), t) -
-                                pl.rec_toff.begin()) - 1;
-            pl.inj_rec.push_back(r);
+            pl.inj_rec.push_back(rec_of[t - pl.rec_toff[pl.rec_off[s]]]);
             pl.inj_w.push_back(pl.rec_tw[t]);
         }
         if (!ct.empty()) pl.inj_off.push_back((int)pl.inj_rec.size());
@@ -463,56 +527,70 @@ smi_status make_plan(const smi_grid *g, const smi_acq *acq, smi_job job, double 
     pl.nsave = !pl.save ? 0 : (g->dr == 1 ? nt : (nt - 1) / g->dr + kTaps + 1);
     pl.nrun = pl.save && g->dr > 1 ? (pl.nsave - 1) * g->dr : nt;
     const int nrun = pl.nrun;
-    pl.fbox.assign((size_t)nrun * ns * 6, 0);
-    pl.abox.assign(pl.adjoint ? (size_t)nt * ns * 6 : 0, 0);
-    pl.rbox.assign(pl.adjoint ? (size_t)nt * ns * 6 : 0, 0);
+    pl.nfbox = (size_t)nrun * ns * 6;
+    pl.nabox = pl.adjoint ? (size_t)nt * ns * 6 : 0;
     pl.cnt_fwd = pl.cnt_adj = pl.cnt_rec = 0;
-    for (int it = 0; it < nrun; ++it)
-        for (int s = 0; s < ns; ++s) {
-            const bool adj_it = pl.adjoint && it < nt;
-            int *fb = &pl.fbox[((size_t)it * ns + s) * 6];
-            double vf = 1, va = 1, vr = 1;
-            for (int a = 0; a < 3; ++a) {
-                int lo = 0, hi = pl.M[a];
-                if (a < pl.nd && g->box) {
-                    int r = (int)std::ceil(vmax * (it + 1) * g->dt / hs[a]) + pl.margin;
-                    lo = std::max(0, pl.src[3 * s + a] - r);
-                    hi = std::min(pl.M[a] - 1, pl.src[3 * s + a] + r) + 1;
-                }
-                fb[2 * a] = lo; fb[2 * a + 1] = hi;
-                vf *= hi - lo;
-                if (adj_it) {
-                    int *ab = &pl.abox[((size_t)it * ns + s) * 6];
-                    int *rb = &pl.rbox[((size_t)it * ns + s) * 6];
-                    int alo = 0, ahi = pl.M[a];
-                    int nr = pl.rec_off[s + 1] - pl.rec_off[s];
-                    if (a < pl.nd && nr == 0) { alo = 0; ahi = 0; }
-                    else if (a < pl.nd && g->box) {
-                        int rmin = 1 << 30, rmax = -1;
-                        for (int r = pl.rec_off[s]; r < pl.rec_off[s + 1]; ++r) {
-                            rmin = std::min(rmin, pl.rec[3 * (size_t)r + a]);
-                            rmax = std::max(rmax, pl.rec[3 * (size_t)r + a]);
-                        }
-                        int w = (int)std::ceil(vmax * (nt - it) * g->dt / hs[a]) + pl.margin;
-                        alo = std::max(0, rmin - w);
-                        ahi = std::min(pl.M[a] - 1, rmax + w) + 1;
-                    }
-                    ab[2 * a] = alo; ab[2 * a + 1] = ahi;
-                    va *= std::max(0, ahi - alo);
-                    int rlo = lo, rhi = hi;
-                    if (a < pl.nd) {
-                        rlo = std::max(lo, g->nb);
-                        rhi = std::min(hi, g->nb + pl.n[a]);
-                    }
-                    if (rhi < rlo) rhi = rlo;
-                    rb[2 * a] = rlo; rb[2 * a + 1] = rhi;
-                    vr *= rhi - rlo;
-                }
-            }
-            pl.cnt_fwd += vf;
-            if (adj_it) { pl.cnt_adj += va; pl.cnt_rec += vr; }
+    // extent of the receivers' nodes per shot and axis
+    std::vector<int> ext((size_t)ns * 6);
+    for (int s = 0; s < ns; ++s) {
+        int *q = &ext[(size_t)s * 6];
+        if (same[s]) {
+            std::copy(q - 6, q, q);
+            continue;
         }
-    algorithmic_bytes(pl);
+        for (int a = 0; a < 3; ++a) { q[2 * a] = 1 << 30; q[2 * a + 1] = -1; }
+        for (int r = pl.rec_off[s]; r < pl.rec_off[s + 1]; ++r)
+            for (int a = 0; a < 3; ++a) {
+                q[2 * a] = std::min(q[2 * a], pl.rec[3 * (size_t)r + a]);
+                q[2 * a + 1] = std::max(q[2 * a + 1], pl.rec[3 * (size_t)r + a]);
+            }
+    }
+    // adjoint box of shot s at step it
+    auto adj_box = [&](int it, int s, int *ab) {
+        for (int a = 0; a < 3; ++a) {
+            int alo = 0, ahi = pl.M[a];
+            if (a < pl.nd && pl.rec_off[s + 1] == pl.rec_off[s]) ahi = 0;
+            else if (a < pl.nd && g->box) {
+                const int w = (int)std::ceil(vmax * (nt - it) * g->dt / hs[a]) + pl.margin;
+                alo = std::max(0, ext[(size_t)s * 6 + 2 * a] - w);
+                ahi = std::min(pl.M[a] - 1, ext[(size_t)s * 6 + 2 * a + 1] + w) + 1;
+            }
+            ab[2 * a] = alo;
+            ab[2 * a + 1] = ahi;
+        }
+    };
+    if (!sizes) {
+        pl.fbox.assign(pl.nfbox, 0);
+        pl.abox.assign(pl.nabox, 0);
+        pl.rbox.assign(pl.nabox, 0);
+        auto volume = [](const int *b) {
+            return (double)std::max(0, b[1] - b[0]) * std::max(0, b[3] - b[2]) * std::max(0, b[5] - b[4]);
+        };
+        for (int it = 0; it < nrun; ++it) {
+            int rad[3] = {0, 0, 0};
+            for (int a = 0; a < pl.nd; ++a) rad[a] = (int)std::ceil(vmax * (it + 1) * g->dt / hs[a]) + pl.margin;
+            for (int s = 0; s < ns; ++s) {
+                int *fb = &pl.fbox[((size_t)it * ns + s) * 6];
+                for (int a = 0; a < 3; ++a) {
+                    const bool boxed = a < pl.nd && g->box;
+                    fb[2 * a] = boxed ? std::max(0, pl.src[3 * s + a] - rad[a]) : 0;
+                    fb[2 * a + 1] = boxed ? std::min(pl.M[a] - 1, pl.src[3 * s + a] + rad[a]) + 1 : pl.M[a];
+                }
+                pl.cnt_fwd += volume(fb);
+                if (!pl.adjoint || it >= nt) continue;
+                int *ab = &pl.abox[((size_t)it * ns + s) * 6], *rb = &pl.rbox[((size_t)it * ns + s) * 6];
+                adj_box(it, s, ab);
+                for (int a = 0; a < 3; ++a) {
+                    rb[2 * a] = a < pl.nd ? std::max(fb[2 * a], g->nb) : fb[2 * a];
+                    rb[2 * a + 1] = a < pl.nd ? std::min(fb[2 * a + 1], g->nb + pl.n[a]) : fb[2 * a + 1];
+                    rb[2 * a + 1] = std::max(rb[2 * a + 1], rb[2 * a]);
+                }
+                pl.cnt_adj += volume(ab);
+                pl.cnt_rec += volume(rb);
+            }
+        }
+        algorithmic_bytes(pl);
+    }
 
     // boundary bands (Sec. 4.2): N planes of p and N of the face-normal v per face
     BandDesc &bd = pl.band;
@@ -593,16 +671,18 @@ smi_status make_plan(const smi_grid *g, const smi_acq *acq, smi_job job, double 
         }
         const int nrow = zhi - zlo + 1;
         bool ok = (size_t)ns * nrow * pl.M[1] <= kInjMapCap;
-        for (int it = 1; ok && it < nt; ++it)
-            for (int s = 0; ok && s < ns; ++s) {
-                const int *q = &bb[4 * (size_t)s];
-                if (q[1] < 0) continue;
-                const int *ab = &pl.abox[((size_t)it * ns + s) * 6];
-                ok = q[0] >= ab[0] && q[1] < ab[1] && q[2] >= ab[2] && q[3] < ab[3];
-            }
+        // the adjoint box only grows from the last step to the first: the last step decides
+        for (int s = 0; ok && nt > 1 && s < ns; ++s) {
+            const int *q = &bb[4 * (size_t)s];
+            if (q[1] < 0) continue;
+            int ab[6];
+            adj_box(nt - 1, s, ab);
+            ok = q[0] >= ab[0] && q[1] < ab[1] && q[2] >= ab[2] && q[3] < ab[3];
+        }
         if (ok) {
-            pl.inj_map.assign((size_t)ns * nrow * pl.M[1], -1);
-            for (int u = 0; u < U; ++u)
+            pl.ninjmap = (size_t)ns * nrow * pl.M[1];
+            if (!sizes) pl.inj_map.assign(pl.ninjmap, -1);
+            for (int u = 0; !sizes && u < U; ++u)
                 pl.inj_map[((size_t)pl.inj_shot[u] * nrow + (nz[u] - zlo)) * pl.M[1] + nx[u]] = u;
             pl.inj_zlo = zlo;
             pl.inj_nrow = nrow;
@@ -644,14 +724,14 @@ size_t layout(Plan &pl, bool side) {
     size_t cp = 0;
     for (int a = 0; a < pl.nd; ++a) cp += 4 * (size_t)pl.M[a];
     pl.off_cpml = take(sizeof(float) * cp);
-    pl.off_tables = take(sizeof(int) * (pl.fbox.size() + pl.abox.size() + pl.rbox.size()));
+    pl.off_tables = take(sizeof(int) * (pl.nfbox + 2 * pl.nabox));
     pl.off_recv = take((size_t)R * (sizeof(int) * 2 + sizeof(long long)) +
                        sizeof(long long) * (size_t)ns + 64);
     pl.off_taps = take(sizeof(int) * (pl.src_toff.size() + pl.rec_toff.size()) +
                        (sizeof(long long) + sizeof(float)) * (pl.src_tcell.size() + pl.rec_tcell.size()) + 64);
     pl.off_inj = take((sizeof(int) * 2 + sizeof(long long)) * pl.inj_cell.size() +
                       (sizeof(int) + sizeof(float)) * pl.inj_rec.size() + 64);
-    pl.off_injmap = take(sizeof(int) * pl.inj_map.size() + 64);
+    pl.off_injmap = take(sizeof(int) * pl.ninjmap + 64);
     size_t fld = sizeof(float) * (size_t)ns * ((size_t)pl.P * (1 + pl.nd) +
                  2 * (size_t)(G.psz[0] + G.psz[1] + G.psz[2]));
     pl.off_fields = take(fld);

@@ -128,6 +128,7 @@ struct Plan {
     std::vector<int> fbox;         // [nt][nshot][6] forward box (lo, hi exclusive per axis)
     std::vector<int> abox;         // [nt][nshot][6] adjoint box
     std::vector<int> rbox;         // [nt][nshot][6] reconstruction region (interior clip)
+    size_t nfbox = 0, nabox = 0;   // entries of fbox, and of abox and rbox (also where left empty)
     // point operators of sources and receivers (Sec. 2.1): the Kaiser-windowed sinc of a
     // point off the grid, or its node with weight 1; CSR over shots / receivers, cells are
     // offsets inside one shot's field.  src_cell[s] is the node of a one-tap source, else -1.
@@ -145,6 +146,7 @@ struct Plan {
     // inj_zlo) M[1] + x] is the node of shot s at padded (z, x), or -1, over the rows
     // [inj_zlo, inj_zlo + inj_nrow) that hold nodes.
     std::vector<int> inj_map;
+    size_t ninjmap = 0;            // its entries (also where left empty)
     int inj_zlo = 0, inj_nrow = 0;
     bool inj_fused = false;
     BandDesc band{};
@@ -182,9 +184,10 @@ struct Plan {
     std::vector<double> rev_bytes;
 };
 
-// Build and validate a plan.  Returns SMI_OK or an error with `err` filled.
+// Build and validate a plan.  Returns SMI_OK or an error with `err` filled.  sizes: only what the
+// workspace layout needs (the box tables, counts and the node map stay empty).
 smi_status make_plan(const smi_grid *g, const smi_acq *acq, smi_job job, double vmin,
-                     double vmax, Plan &pl, std::string &err);
+                     double vmax, Plan &pl, std::string &err, bool sizes = false);
 // lay the workspace out, with the side rows of the pipelined 2D step or without; its size
 size_t layout(Plan &pl, bool side);
 smi_status check_grid(const smi_grid *g, double vmin, double vmax, std::string &err);
