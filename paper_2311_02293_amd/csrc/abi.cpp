@@ -1243,7 +1243,15 @@ smi_status smi_born(smi_ctx *ctx, const smi_grid *grid, const smi_acq *acq, cons
     smi::StepCtx c{&pl, &w, stf, st, false};
     configure(c, ctx, pl);
     c.plain = false;
-    for (int it = 0; it < pl.g.nt; ++it) {
+    const bool pair = ctx->opt_kernel == 0 && smi::born_pair_available(c);
+    for (int it = 0; it < pl.g.nt && pair; ++it) {
+        HIPCHK(smi::born_pair(c, it, dkappa), "tangent-linear step");
+        HIPCHK(smi::src_taps(c, it, w.f.p, 1.f), "source");
+        c.ext_it = it;
+        c.ext_dcal = ddata;
+    }
+    if (pair) HIPCHK(smi::extract(c, pl.g.nt - 1, ddata, w.q.p), "extract");
+    for (int it = 0; it < pl.g.nt && !pair; ++it) {
         HIPCHK(smi::fwd_step(c, it), "background step");
         HIPCHK(smi::src_taps(c, it, w.f.p, 1.f), "source");
         HIPCHK(smi::born_step(c, it, dkappa), "perturbation step");

@@ -541,18 +541,53 @@ struct InjArg {
     float inv_dt;
 };
 
+// the secondary source of a tangent-linear p update (2D): the background's velocities and dkappa
+struct BornArg {
+    const float *vz, *vx;   // of shot 0
+    const float *dkap;
+};
+
+// div v^{it+1/2} of the background (without memory variables) at the cells of a lane, for the
+// secondary source of its perturbation update; loads first, as the update itself
+template <int N, int CM>
+__device__ __forceinline__ void born_div(const Geom &g, const BornArg &ba, long long k0, int cnt,
+                                         float (&div)[CM]) {
+    constexpr int NW = CM + 2 * N - 1;
+    float w[NW], st[CM][2 * N];
+#pragma unroll
+    for (int j = 0; j < NW; ++j) w[j] = ba.vx[k0 + min(j - N, cnt - 1 + N - 1) * (long long)g.ld1];
+#pragma unroll
+    for (int t = 0; t < CM; ++t)
+#pragma unroll
+        for (int j = 0; j < 2 * N; ++j) st[t][j] = ba.vz[k0 + min(t, cnt - 1) * (long long)g.ld1 + j - N];
+#pragma unroll
+    for (int t = 0; t < CM; ++t) {
+        float ez = 0.f, ex = 0.f;
+#pragma unroll
+        for (int l = 1; l <= N; ++l) {
+            ez += g.c[0][l - 1] * (st[t][N + l - 1] - st[t][N - l]);
+            ex += g.c[1][l - 1] * (w[t + N + l - 1] - w[t + N - l]);
+        }
+        div[t] = 0.f;
+        div[t] += ez;
+        div[t] += ex;
+    }
+}
+
 // p -= dt kappa sum_a (D-_a v_a + psi_a) [+ source] [image] (eq. 3 second row, CPML); loads
 // first, as in k_march_v.  INJ (2D adjoint update): p~ then takes the adjoint sources of the
 // next reverse level at the nodes, after the image has read it (a pass of its own after the
 // update, so that the update keeps its registers and schedule).  FS: free surface (the lanes
-// near it write the surface row and the image rows of p).
-template <int ND, int N, int CM, bool ZL, bool SRC, bool IMG, bool INJ = false, bool FS = false>
+// near it write the surface row and the image rows of p).  BORN (2D perturbation field of the
+// tangent-linear step): p~ also takes -dt dkappa div v of the background on the interior.
+template <int ND, int N, int CM, bool ZL, bool SRC, bool IMG, bool INJ = false, bool FS = false,
+          bool BORN = false>
 __device__ __forceinline__ void march_p_body(Geom g, Fields f, Model m, Cpml cp,
                                                  const int *__restrict__ box, int shot0, MG mg,
                                                  const long long *__restrict__ src_cell,
                                                  const float *__restrict__ stf, int nt, int it,
                                                  const float *__restrict__ pf, float *acc_i, BandArg sv, int sv_z0,
-                                                 InjArg ia = InjArg{}) {
+                                                 InjArg ia = InjArg{}, BornArg bo = BornArg{}) {
     // the v band cells of the next level (the p update leaves v alone), on the planes from sv_z0
     if (sv.buf && (int)blockIdx.z >= sv_z0) {
         band_part(g, f, sv, sv_z0, 0, 1);
@@ -569,6 +604,12 @@ __device__ __forceinline__ void march_p_body(Geom g, Fields f, Model m, Cpml cp,
     const long long so0 = mc.s * g.P;
     const float *__restrict__ vm = f.v[MA] + so0;
     const long long k0 = as_cell<ND>(g, mc, mc.lo).k;
+    float bdiv[CM];
+    if constexpr (BORN && ND == 2) {
+        bo.vz += so0;
+        bo.vx += so0;
+        born_div<N, CM>(g, bo, k0, cnt, bdiv);
+    }
     float w[NW];
 #pragma unroll
     for (int j = 0; j < NW; ++j) w[j] = mc.ok ? vm[k0 + min(j - N, cnt - 1 + N - 1) * ms] : 0.f;
@@ -631,6 +672,11 @@ __device__ __forceinline__ void march_p_body(Geom g, Fields f, Model m, Cpml cp,
         }
         float pn = po[t] - kd[t] * sdiv;
         if (SRC && it < nt && c.k == sc) pn += src_amp(g.src_scale, stf[(long long)c.s * nt + it]);
+        if constexpr (BORN && ND == 2) {
+            const int iz = c.z - g.nb, ix = c.x - g.nb;
+            if ((unsigned)iz < (unsigned)g.n[0] && (unsigned)ix < (unsigned)g.n[1])
+                pn -= g.dt * bo.dkap[iz + (long long)g.n[0] * ix] * bdiv[t];
+        }
         float *pd = f.p + so0 + c.k;
         if (FS) {
             // free surface (image method): p = 0 on row nb and odd about it, the rows nb - N ..
@@ -682,6 +728,40 @@ __global__ __launch_bounds__(256) void k_march_p(Geom g, Fields f, Model m, Cpml
                                                  const float *__restrict__ pf, float *acc_i, BandArg sv, int sv_z0) {
     march_p_body<ND, N, CM, ZL, SRC, IMG, false, FS>(g, f, m, cp, box, shot0, mg, src_cell, stf, nt,
                                                      it, pf, acc_i, sv, sv_z0);
+}
+
+// The tangent-linear step of the 2D default path in two launches: the v updates of the background
+// and of the perturbation on disjoint planes of one grid (the perturbation's receivers of the
+// previous step in front), then their p updates, the perturbation's with the secondary source.  A
+// step of one launch per part (five or more, and one for the receivers) spent its time on launches:
+// 220 x 640, order 8, 4 shots, 1000 steps 29.4 -> 15.5 ms.
+template <int N, int CM, bool FS>
+__global__ __launch_bounds__(256) void k_born_v(Geom g, Fields f, Fields q, Model m, Cpml cp,
+                                                const int *__restrict__ box, MG mg, int front,
+                                                int nshot, Ext ex) {
+    const int bz = (int)blockIdx.z;
+    const Ext none{Recv{}, nullptr, -1, nullptr};
+    if (bz < front)
+        march_v_body<2, N, CM, false, FS>(g, q, m, cp, box, 0, mg, ex, BandArg{}, 0);
+    else if (bz < front + nshot)
+        march_v_body<2, N, CM, false, FS>(g, f, m, cp, box, -front, mg, none, BandArg{}, 0);
+    else
+        march_v_body<2, N, CM, false, FS>(g, q, m, cp, box, -front - nshot, mg, none, BandArg{}, 0);
+}
+
+template <int N, int CM, bool FS>
+__global__ __launch_bounds__(256) void k_born_p(Geom g, Fields f, Fields q, Model m, Cpml cp,
+                                                const int *__restrict__ box, MG mg, int nshot,
+                                                const long long *__restrict__ src_cell,
+                                                const float *__restrict__ stf, int nt, int it,
+                                                const float *__restrict__ dkap) {
+    if ((int)blockIdx.z < nshot)
+        march_p_body<2, N, CM, false, true, false, false, FS>(g, f, m, cp, box, 0, mg, src_cell, stf,
+                                                              nt, it, nullptr, nullptr, BandArg{}, 0);
+    else
+        march_p_body<2, N, CM, false, false, false, false, FS, true>(
+            g, q, m, cp, box, -nshot, mg, src_cell, stf, nt, it, nullptr, nullptr, BandArg{}, 0,
+            InjArg{}, BornArg{f.v[0], f.v[1], dkap});
 }
 
 // ---------------------------------------------------------------- reconstruction (Sec. 4.2)
@@ -1921,6 +2001,38 @@ hipError_t rho_faces_t(const StepCtx &c, int it) {
 
 hipError_t rho_faces(const StepCtx &c, int it) { SMI_DISPATCH(rho_faces_t, c, it); }
 
+template <int N>
+hipError_t born_pair_t(const StepCtx &c, int it, const float *dkappa) {
+    constexpr int CM = 4;
+    const Plan &pl = *c.pl;
+    const Views &w = *c.w;
+    const int *box = w.fbox + (size_t)it * pl.nshot * 6;
+    const MLaunch L = march_launch(pl, pl.fbox, it, 0, pl.nshot, CM, c.xcd, false, false);
+    const int front = c.ext_it >= 0 && w.recv.R > 0 ? 1 : 0;
+    const Ext ex{w.recv, c.ext_dcal, c.ext_it, w.status};
+    dim3 gv = L.grid, gp = L.grid;
+    gv.z = (unsigned)(front + 2 * pl.nshot);
+    gp.z = (unsigned)(2 * pl.nshot);
+    auto launch = [&](auto fs) -> hipError_t {
+        constexpr bool F = decltype(fs)::value;
+        hipLaunchKernelGGL((k_born_v<N, CM, F>), gv, L.block, 0, c.st, pl.geom, w.f, w.q, w.model,
+                           w.cpml, box, L.mg, front, pl.nshot, ex);
+        hipLaunchKernelGGL((k_born_p<N, CM, F>), gp, L.block, 0, c.st, pl.geom, w.f, w.q, w.model,
+                           w.cpml, box, L.mg, pl.nshot, (const long long *)w.src_cell, c.stf,
+                           pl.g.nt, it, dkappa);
+        return hipGetLastError();
+    };
+    return pl.g.freesurf ? launch(std::true_type{}) : launch(std::false_type{});
+}
+
+bool born_pair_available(const StepCtx &c) {
+    return c.pl->nd == 2 && !c.plain && c.march == 4 && !c.zl && !c.step2d;
+}
+
+hipError_t born_pair(const StepCtx &c, int it, const float *dkappa) {
+    return c.pl->N == 2 ? born_pair_t<2>(c, it, dkappa) : born_pair_t<4>(c, it, dkappa);
+}
+
 template <int ND, int N>
 hipError_t born_step_t(const StepCtx &c, int it, const float *dkappa) {
     const Plan &pl = *c.pl;
@@ -1928,12 +2040,17 @@ hipError_t born_step_t(const StepCtx &c, int it, const float *dkappa) {
     const int *box = w.fbox + (size_t)it * pl.nshot * 6;
     Launch L = box_launch(pl, pl.fbox, it, 0, pl.nshot, c.xcd);
     if (L.empty) return hipSuccess;
-    hipLaunchKernelGGL((k_step_v<ND, N>), L.grid, L.block, 0, c.st, pl.geom, w.q, w.model,
-                       w.cpml, box, 0, L.ey);
-    SMI_TRY(fs_launch(pl, c.st, w.q.v[0], 0, 0, pl.nshot));
-    hipLaunchKernelGGL((k_step_p<ND, N, false, false>), L.grid, L.block, 0, c.st, pl.geom, w.q,
-                       w.model, w.cpml, box, 0, L.ey, (const long long *)w.src_cell, c.stf,
-                       pl.g.nt, it, (const float *)nullptr, (float *)nullptr);
+    if (ND == 3 && c.y3) {
+        // the y-marching half steps, as the background's
+        SMI_TRY(pert_step_y3(c, it));
+    } else {
+        hipLaunchKernelGGL((k_step_v<ND, N>), L.grid, L.block, 0, c.st, pl.geom, w.q, w.model,
+                           w.cpml, box, 0, L.ey);
+        SMI_TRY(fs_launch(pl, c.st, w.q.v[0], 0, 0, pl.nshot));
+        hipLaunchKernelGGL((k_step_p<ND, N, false, false>), L.grid, L.block, 0, c.st, pl.geom, w.q,
+                           w.model, w.cpml, box, 0, L.ey, (const long long *)w.src_cell, c.stf,
+                           pl.g.nt, it, (const float *)nullptr, (float *)nullptr);
+    }
     hipLaunchKernelGGL((k_born_src<ND, N>), L.grid, L.block, 0, c.st, pl.geom, w.f, w.q, box, 0,
                        L.ey, dkappa);
     hipError_t e = hipGetLastError();

@@ -303,6 +303,8 @@ bool march_forward(const StepCtx &c);
 bool y3_available(const Plan &pl);
 hipError_t fwd_step_y3(const StepCtx &c, int it);
 hipError_t adj_step_y3(const StepCtx &c, int it, bool image);
+// perturbation field of the tangent-linear step over the forward boxes
+hipError_t pert_step_y3(const StepCtx &c, int it);
 bool yp_available(const Plan &pl);
 hipError_t fwd_step_yp(const StepCtx &c, int it);
 hipError_t adj_step_yp(const StepCtx &c, int it, bool image);
@@ -349,6 +351,10 @@ hipError_t rho_faces(const StepCtx &c, int it);
 // tangent-linear step: the perturbation field (q) over the forward box, with the secondary
 // source -dt dkappa div v of the background (f, after its own step)
 hipError_t born_step(const StepCtx &c, int it, const float *dkappa);
+// 2D default path: background and perturbation step in two launches, with the perturbation's
+// receivers of step c.ext_it
+bool born_pair_available(const StepCtx &c);
+hipError_t born_pair(const StepCtx &c, int it, const float *dkappa);
 // gradients of a parametrisation family (1: Vp, rho; 2: Vp, Ip) from the kappa and face sums
 hipError_t finalize_family(const StepCtx &c, const float *vp, const float *rho, int family,
                            float *g1, float *g2, int s0, int s1);

@@ -318,12 +318,12 @@ hipError_t fwd_y3_t(const StepCtx &c, int it) {
     return pl.g.freesurf ? launch(std::true_type{}) : launch(std::false_type{});
 }
 
+// half steps of the second field (w.q) over the boxes `tab` (its device copy `ab`)
 template <int N, int BX, int CY>
-hipError_t adj_y3_t(const StepCtx &c, int it, bool image) {
+hipError_t adj_y3_t(const StepCtx &c, int it, bool image, const std::vector<int> &tab, const int *ab) {
     const Plan &pl = *c.pl;
     const Views &w = *c.w;
-    const int *ab = w.abox + (size_t)it * pl.nshot * 6;
-    YLaunch L = y3_launch(pl, pl.abox, it, BX, CY);
+    YLaunch L = y3_launch(pl, tab, it, BX, CY);
     if (L.empty) return hipSuccess;
     auto launch = [&](auto fs) -> hipError_t {
         constexpr bool F = decltype(fs)::value;
@@ -372,7 +372,14 @@ hipError_t fwd_step_y3(const StepCtx &c, int it) {
 
 hipError_t adj_step_y3(const StepCtx &c, int it, bool image) {
     const Plan &pl = *c.pl;
-    SMI_Y3(adj_y3_t, c, it, image);
+    const int *ab = c.w->abox + (size_t)it * pl.nshot * 6;
+    SMI_Y3(adj_y3_t, c, it, image, pl.abox, ab);
+}
+
+hipError_t pert_step_y3(const StepCtx &c, int it) {
+    const Plan &pl = *c.pl;
+    const int *fb = c.w->fbox + (size_t)it * pl.nshot * 6;
+    SMI_Y3(adj_y3_t, c, it, false, pl.fbox, fb);
 }
 
 }  // namespace smi
