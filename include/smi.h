@@ -108,7 +108,7 @@ typedef enum {
                                 results; not with snapshots or
                                 SMI_OPT_TIMING, nor with receivers whose nodes span
                                 more than 16 rows); in 3D the forward and adjoint
-                                half steps of 5 (marching along y, SMI_OPT_CHUNK 432) where
+                                half steps of 5 (marching along y, SMI_OPT_CHUNK 0) where
                                 they apply, register-blocked kernels with 2 cells per lane
                                 elsewhere;
                                 1: plain stepper -- one shot per launch, one cell per lane;
@@ -119,7 +119,8 @@ typedef enum {
                                 lane sweep kernels in the order of SMI_OPT_TILEMAP; 5: as 0, and
                                 in 3D half steps that march along y (SMI_OPT_CHUNK = 100 BX + CY:
                                 BX = 4 or 8 x-columns of 64 z cells per wavefront, CY = 16,
-                                32 or 64 y-planes per workgroup, 32 at order 4; 0: 432); 6: as 0,
+                                32 or 64 y-planes per workgroup, 32 at order 4; 0: BX 4 and 4
+                                to 32 planes, fewer where a launch has few tiles); 6: as 0,
                                 and in 2D forward passes the fused marching step (v and p of
                                 every shot in one launch, levels in two buffers, SMI_OPT_CHUNK
                                 = 100 D + C: runs of C = 32 or 64 columns per wavefront, loads

@@ -182,9 +182,9 @@ void configure(smi::StepCtx &c, const smi_ctx *ctx, const Plan &pl) {
     c.depth = 2;
     c.yp = 0;
     // 3D forward and adjoint half steps of options 0, 6 and 7: the y-marching kernels (4-column
-    // tiles, 32 planes per workgroup) wherever they apply -- 8.5 % faster on the whole 3D RTM and
+    // tiles, up to 32 planes per workgroup) wherever they apply -- 8.5 % faster on the whole 3D RTM and
     // 15 % on the full-grid step than the register-blocked kernels, which remain option 3
-    const int y3_default = pl.nd == 3 && smi::y3_available(pl) ? 432 : 0;
+    const int y3_default = pl.nd == 3 && smi::y3_available(pl) ? 400 : 0;
     if (ctx->opt_kernel == 0 || ctx->opt_kernel == 6 || ctx->opt_kernel == 7) {
         c.y3 = y3_default;
         // the register-blocked 3D kernels (the reconstruction, and every half step where the
@@ -232,7 +232,7 @@ void configure(smi::StepCtx &c, const smi_ctx *ctx, const Plan &pl) {
     } else if (ctx->opt_kernel == 5) {
         c.march = pl.nd == 2 ? 4 : 2;
         c.xcd = pl.nd == 2;
-        c.y3 = smi::y3_available(pl) ? (ctx->opt_chunk > 0 ? ctx->opt_chunk : 432) : 0;
+        c.y3 = smi::y3_available(pl) ? (ctx->opt_chunk > 0 ? ctx->opt_chunk : 400) : 0;
     }
 }
 
@@ -476,7 +476,7 @@ std::vector<Cand> fwd_candidates(const Plan &pl) {
         if (smi::yp_available(pl)) {
             v.push_back({2, false, false, false, 32, 2, "yplane-2x8", 32});
         }
-        if (smi::y3_available(pl)) v.push_back({2, false, false, false, 32, 2, "ymarch-4x32", 0, 432});
+        if (smi::y3_available(pl)) v.push_back({2, false, false, false, 32, 2, "ymarch-4", 0, 400});
     }
     return v;
 }

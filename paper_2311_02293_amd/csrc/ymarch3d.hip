@@ -344,14 +344,39 @@ hipError_t adj_y3_t(const StepCtx &c, int it, bool image, const std::vector<int>
     return pl.g.freesurf ? launch(std::true_type{}) : launch(std::false_type{});
 }
 
-// tiles: y3 = 100 BX + CY with BX in {4, 8} and CY in {16, 32, 64}; others fall back to 832
-#define SMI_Y3(fn, ...)                                                                       \
+// Planes per workgroup of the default: a strip of CY planes is a serial march with two barriers per
+// plane, so a box of few tiles leaves the chip waiting on it.  From 32 planes the strips are halved,
+// down to 4, until 16384 workgroups are launched (64 per CU; a shorter strip loads its 2N - 1
+// planes of window more often, which the L2 absorbs).  Against 32 planes throughout: one shot on
+// 260^3, order 8, box on, 500 steps 93.6 -> 74.0 ms (75.4 with 8 planes at least, 81.3 with
+// 2048 workgroups); 3D image 200 x 220 x 210, 2 shots 305 -> 264 ms; order-4 gradient 97 x 111 x
+// 103, 2 shots 99.2 -> 73.3 ms; full 400^3 grid, 4 shots, where 32 planes stay, 4.51 ms per step.
+int y3_planes(const Plan &pl, const std::vector<int> &tab, int it, int bx) {
+    int cy = 32;
+    while (cy > 4) {
+        const YLaunch L = y3_launch(pl, tab, it, bx, cy);
+        if ((long long)L.grid.x * L.grid.y * L.grid.z >= 16384) break;
+        cy /= 2;
+    }
+    return cy;
+}
+
+// tiles: y3 = 100 BX + CY with BX in {4, 8} and CY in {16, 32, 64} (32 at order 4), others fall back
+// to 832; y3 = 400: BX 4 and the planes of y3_planes over the boxes `tab` of the launch
+#define SMI_Y3(fn, tab, ...)                                                                  \
     do {                                                                                      \
-        const int bx_ = c.y3 / 100, cy_ = c.y3 % 100;                                         \
+        const int bx_ = c.y3 / 100;                                                           \
+        const bool fit_ = c.y3 == 400;                                                        \
+        const int cy_ = fit_ ? y3_planes(pl, tab, it, 4) : c.y3 % 100;                        \
         if (pl.N == 2) {                                                                      \
+            if (fit_ && cy_ == 4) return fn<2, 4, 4>(__VA_ARGS__);                            \
+            if (fit_ && cy_ == 8) return fn<2, 4, 8>(__VA_ARGS__);                            \
+            if (fit_ && cy_ == 16) return fn<2, 4, 16>(__VA_ARGS__);                          \
             if (bx_ == 4) return fn<2, 4, 32>(__VA_ARGS__);                                   \
             return fn<2, 8, 32>(__VA_ARGS__);                                                 \
         }                                                                                     \
+        if (fit_ && cy_ == 4) return fn<4, 4, 4>(__VA_ARGS__);                                \
+        if (fit_ && cy_ == 8) return fn<4, 4, 8>(__VA_ARGS__);                                \
         if (bx_ == 4 && cy_ == 16) return fn<4, 4, 16>(__VA_ARGS__);                          \
         if (bx_ == 4 && cy_ == 32) return fn<4, 4, 32>(__VA_ARGS__);                          \
         if (bx_ == 4 && cy_ == 64) return fn<4, 4, 64>(__VA_ARGS__);                          \
@@ -367,19 +392,19 @@ bool y3_available(const Plan &pl) { return pl.nd == 3; }
 
 hipError_t fwd_step_y3(const StepCtx &c, int it) {
     const Plan &pl = *c.pl;
-    SMI_Y3(fwd_y3_t, c, it);
+    SMI_Y3(fwd_y3_t, pl.fbox, c, it);
 }
 
 hipError_t adj_step_y3(const StepCtx &c, int it, bool image) {
     const Plan &pl = *c.pl;
     const int *ab = c.w->abox + (size_t)it * pl.nshot * 6;
-    SMI_Y3(adj_y3_t, c, it, image, pl.abox, ab);
+    SMI_Y3(adj_y3_t, pl.abox, c, it, image, pl.abox, ab);
 }
 
 hipError_t pert_step_y3(const StepCtx &c, int it) {
     const Plan &pl = *c.pl;
     const int *fb = c.w->fbox + (size_t)it * pl.nshot * 6;
-    SMI_Y3(adj_y3_t, c, it, false, pl.fbox, fb);
+    SMI_Y3(adj_y3_t, pl.fbox, c, it, false, pl.fbox, fb);
 }
 
 }  // namespace smi
