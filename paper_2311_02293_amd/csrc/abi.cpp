@@ -154,6 +154,7 @@ void apply_pick(smi::StepCtx &c, const smi_ctx *ctx, const Plan &pl, bool forwar
         c.ymap = p.ymap;
         c.step2d = p.step2d;
         c.steps = p.steps;
+        c.fit = false;
         c.run = p.run;
         c.depth = p.depth;
         c.yp = p.yp;
@@ -178,6 +179,7 @@ void configure(smi::StepCtx &c, const smi_ctx *ctx, const Plan &pl) {
     c.rev = ctx->opt_rev;
     c.step2d = false;
     c.steps = false;
+    c.fit = false;
     c.run = 32;
     c.depth = 2;
     c.yp = 0;
@@ -218,6 +220,7 @@ void configure(smi::StepCtx &c, const smi_ctx *ctx, const Plan &pl) {
         c.march = pl.nd == 2 ? 4 : 2;
         c.xcd = pl.nd == 2;
         c.steps = smi::steps2d_default(pl);
+        c.fit = pl.nd == 2;
     } else if (ctx->opt_kernel == 2) {
         c.march = ctx->opt_chunk % 100 == 8 ? 8 : 4;
         c.zl = ctx->opt_chunk >= 100;   // the tiled variant of the fused step
@@ -280,7 +283,7 @@ Key plan_key(char tag, const Plan &pl, const smi::StepCtx &c) {
     Key k;
     k.put(tag).put(pl.geom).put(pl.band).put(pl.nshot).put(pl.nrun).put(pl.nsave);
     k.put(pl.save).put(pl.g.nt).put(pl.g.dr).put(c.plain).put(c.march).put(c.xcd).put(c.zl).put(c.rev).put(c.ymap);
-    k.put(c.y3).put(pl.chunk).put(c.steps).put(c.step2d).put(c.run).put(c.depth).put(c.yp);
+    k.put(c.y3).put(pl.chunk).put(c.steps).put(c.fit).put(c.step2d).put(c.run).put(c.depth).put(c.yp);
     k.vec(pl.fbox).vec(pl.abox).vec(pl.rbox).vec(pl.rec_off);
     k.put(pl.src_multi).vec(pl.src_toff).vec(pl.src_cell).vec(pl.inj_off);
     k.put(pl.inj_fused).put(pl.inj_zlo).put(pl.inj_nrow).put(pl.rec_zlo).put(pl.rec_nrow);
@@ -487,6 +490,7 @@ void set_cand(smi::StepCtx &c, const Cand &q) {
     c.ymap = q.ymap;
     c.step2d = q.step2d;
     c.steps = q.steps;
+    c.fit = false;
     c.run = q.run;
     c.depth = q.depth;
     c.yp = q.yp;

@@ -269,6 +269,7 @@ struct StepCtx {
     bool xcd = false;       // XCD-contiguous tile order of the sweep kernels
     bool ymap = false;      // 3D register-blocked kernels: XCD-contiguous z-fastest tile order
     int march = 0;          // > 0: register-blocked kernels with this many cells per lane (2, 4, 8)
+    bool fit = false;       // the default: cells per lane of 2D forward half steps by their size
     bool zl = false;        // register-blocked kernels take z-neighbours from LDS
     int y3 = 0;             // 3D: half steps marching along y, tile code 100 BX + CY (0: off)
     int yp = 0;             // 3D: plane-tiled half steps marching along y, CY planes (0: off)
