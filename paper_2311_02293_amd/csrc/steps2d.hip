@@ -43,6 +43,11 @@ namespace {
 
 constexpr unsigned kOut = 0x80000000u;    // a lane offset past every buffer: reads 0, writes nothing
 
+// sum of two lane offsets of which either, or both, may be kOut: never wraps back into the buffer
+__device__ __forceinline__ unsigned add_out(unsigned a, unsigned b) {
+    return __builtin_elementwise_add_sat(a, b);
+}
+
 struct SG {
     int nshot, s0;      // shots of the launch, the first of them (boxes and fields count from 0)
     int nall;           // shots of the plan (stride of the box table)
@@ -264,8 +269,8 @@ __device__ __forceinline__ void march(const Geom &g, const Fields &A, const Fiel
             L.uz = bld(rs, vq, auz + wzb * gcol(k - H));
         }
         if (XE) {
-            L.qx = bld(rs, vxq + lds.xo[k - N - ks], aqx);
-            L.ux = bld(rs, vxq + lds.xo[k - H - ks], aux);
+            L.qx = bld(rs, add_out(vxq, lds.xo[k - N - ks]), aqx);
+            L.ux = bld(rs, add_out(vxq, lds.xo[k - H - ks]), aux);
         }
     };
     // what the source adds to this lane's p of step l at column c
@@ -329,7 +334,7 @@ __device__ __forceinline__ void march(const Geom &g, const Fields &A, const Fiel
                     if (XE) {
                         const float nx = __builtin_fmaf(ah[l].y, l == 0 ? c.qx : ldsr(&lds.rx[0][sv][lane]), ah[l].x * ex);
                         if (l + 1 < T) lds.rx[0][sv][lane] = nx;
-                        else bst(rs, ACT < 2 * T && cv < x0 ? kOut : vxw + lds.xo[cv - ks], aqx + dst, nx);
+                        else bst(rs, ACT < 2 * T && cv < x0 ? kOut : add_out(vxw, lds.xo[cv - ks]), aqx + dst, nx);
                         ex += nx;
                     }
                     vz[l][sv] = (l == 0 ? c.vz : vz[l ? l - 1 : 0][sv]) - c.bz[l] * ez;
@@ -354,7 +359,7 @@ __device__ __forceinline__ void march(const Geom &g, const Fields &A, const Fiel
                     if (XE) {
                         const float nx = __builtin_fmaf(ai[l].y, l == 0 ? c.ux : ldsr(&lds.rx[1][sp][lane]), ai[l].x * ex);
                         if (l + 1 < T) lds.rx[1][sp][lane] = nx;
-                        else bst(rs, vxw + lds.xo[cq - ks], aux + dst, nx);
+                        else bst(rs, add_out(vxw, lds.xo[cq - ks]), aux + dst, nx);
                         ex += nx;
                     }
                     float sdiv = 0.f;

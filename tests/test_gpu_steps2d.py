@@ -84,6 +84,16 @@ def test_two_step_launches_equal_half_steps(ctx, n1, n2, nt, nshot, order, frees
                                         rho_grad=True)))
 
 
+@pytest.mark.parametrize("order,off,nb", [(4, 0, 20), (8, 1, 8)])
+def test_long_run_through_the_absorbing_layers(ctx, order, off, nb):
+    """Long enough for what the layers let through to come back from their outer corners to the
+    receivers: memory variables there stay those of the half-step kernels."""
+    job = _job(60, 64, 1500, 1, order, 0, off, 0)
+    job.grid.nb = nb
+    vp, rho, stf = dev(job)
+    _same(ctx, f"long run order {order}", lambda: [ctx.forward(job.grid, job.acq, vp, rho, stf)[0]])
+
+
 @pytest.mark.parametrize("nrow", [16, 17])
 def test_receiver_rows_up_to_the_limit(ctx, nrow):
     """Receivers spread over 16 rows (kept by the launches) and 17 (the half-step kernels)."""
