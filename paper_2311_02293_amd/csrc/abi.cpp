@@ -821,6 +821,7 @@ smi_status run_reverse(smi_ctx *ctx, smi_state *stt, const float *G, float *grad
     smi::StepCtx c{&pl, &w, stt->stf, st, false};
     configure(c, ctx, pl);
     apply_pick(c, ctx, pl, false);
+    c.rho = want_r;
     for (int k = 0; k < nsnap; ++k)
         if (snap_it[k] == pl.g.nt) HIPCHK(smi::snap(c, w.f, snaps, k, nsnap), "snap");
     // 2D: the reverse loop runs once per group of shots, each group small enough that its
@@ -843,7 +844,7 @@ smi_status run_reverse(smi_ctx *ctx, smi_state *stt, const float *G, float *grad
             c.s0 = rg[gi];
             c.s1 = rg[gi + 1];
             // the adjoint sources of this level were added by the previous reverse step
-            bool injected = false;
+            bool injected = false, faces = false;
             for (int it = pl.g.nt - 1; it >= 0; --it) {
                 // sampled reverse step: the device stamps an event before its first launch and
                 // after its last
@@ -875,15 +876,15 @@ smi_status run_reverse(smi_ctx *ctx, smi_state *stt, const float *G, float *grad
                     rt.form.push_back(rt.form.size() % 2 ? 2 : 1);
                     c.rev = rt.form.back();
                     HIPCHK(hipEventRecord(e0, ls), "tuning event");
-                    HIPCHK(smi::rev_step(c, it, want_g, want_i, adj ? G : nullptr, &injected),
+                    HIPCHK(smi::rev_step(c, it, want_g, want_i, adj ? G : nullptr, &injected, &faces),
                            "reverse step");
                     HIPCHK(hipEventRecord(e1, ls), "tuning event");
                     c.rev = base_rev;
                 } else {
-                    HIPCHK(smi::rev_step(c, it, want_g, want_i, adj ? G : nullptr, &injected),
+                    HIPCHK(smi::rev_step(c, it, want_g, want_i, adj ? G : nullptr, &injected, &faces),
                            "reverse step");
                 }
-                if (want_r) HIPCHK(smi::rho_faces(c, it), "density faces");
+                if (want_r && !faces) HIPCHK(smi::rho_faces(c, it), "density faces");
                 if (ev) HIPCHK(hipEventRecord(ev[1], ls), "timing event");
                 for (int k = 0; k < nsnap; ++k)
                     if (snap_it[k] == it) HIPCHK(smi::snap(c, w.f, snaps, k, nsnap), "snap");

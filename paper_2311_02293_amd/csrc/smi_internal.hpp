@@ -274,6 +274,7 @@ struct StepCtx {
     int y3 = 0;             // 3D: half steps marching along y, tile code 100 BX + CY (0: off)
     int yp = 0;             // 3D: plane-tiled half steps marching along y, CY planes (0: off)
     bool steps = false;     // 2D forward: kSteps time steps per launch (steps2d.hip)
+    bool rho = false;       // the reverse pass keeps the density face sums
     int rev = 0;            // 2D reverse step: 0 by batch size, 1 two launches, 2 five launches
     bool step2d = false;    // 2D forward: the fused marching step (step2d.hip), levels in two buffers
     int run = 32;           // its run of columns per wavefront or tile (32 or 64)
@@ -338,9 +339,10 @@ hipError_t snap(const StepCtx &c, const Fields &f, float *snaps, int k, int nsna
 hipError_t scale_copy(const StepCtx &c, const float *in, float *out, float a);
 hipError_t adj_inject(const StepCtx &c, int it, const float *G);
 // reverse step it; with Gn (the adjoint sources) and it > 0, a step that can also adds the
-// injection of step it - 1 (Plan::inj_fused) and sets *fused, so the caller skips that launch
+// injection of step it - 1 (Plan::inj_fused) and sets *fused, so the caller skips that launch; the
+// same for the density face sums of step it, with c.rho, and *rho
 hipError_t rev_step(const StepCtx &c, int it, bool grad, bool image, const float *Gn = nullptr,
-                    bool *fused = nullptr);
+                    bool *fused = nullptr, bool *rho = nullptr);
 // residual, G = dt r and misfit of the shots [s0, s1) (their slice of dcal / dobs / G)
 hipError_t residual(const StepCtx &c, const float *dcal, const float *dobs, float *G,
                     double *misfit, int s0, int s1);
