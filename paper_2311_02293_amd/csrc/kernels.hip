@@ -1728,9 +1728,8 @@ hipError_t recon_march_t(const StepCtx &c, int it, bool grad, bool image) {
 
 // the two-launch reverse step of the 2D default path (see k_rev_pv); G: the adjoint sources
 // of level it - 1 join the second launch (k_rev_vp with INJ), or null
-template <int N>
+template <int N, int CM>
 hipError_t rev_pair_t(const StepCtx &c, int it, bool grad, bool image, const float *G) {
-    constexpr int CM = 4;
     const Plan &pl = *c.pl;
     const Views &w = *c.w;
     const int *rb = w.rbox + (size_t)it * pl.nshot * 6;
@@ -1824,7 +1823,17 @@ hipError_t rev_step_t(const StepCtx &c, int it, bool grad, bool image, const flo
             const bool inj = Gn && it > 0 && pl.inj_fused;
             if (fused) *fused = inj;
             if (rho) *rho = c.rho;
-            return rev_pair_t<N>(c, it, grad, image, inj ? Gn : nullptr);
+            // Two cells per lane up to 0.8 M padded cells per launch, where the launch has fewer
+            // than four wavefronts per SIMD and lasts as long as one of them (four cells hold
+            // twice the loads of a serial lane).  Order 8, gradient of 800 steps, four -> two
+            // cells: 0.06 M padded cells 14.57 -> 12.95 ms, 0.37 M 15.57 -> 14.01, 0.74 M
+            // 18.03 -> 17.46; slower above (1.1 M 20.68 -> 20.97, 2.2 M 29.5 -> 32.0, 3.3 M
+            // 36.7 -> 42.0), where the cells of a lane share their x stencil's loads.  Order 4
+            // the same within 2 %.
+            constexpr double kFewCells = 0.8e6;
+            const bool few = (double)(se - sa) * (double)pl.P <= kFewCells;
+            return few ? rev_pair_t<N, 2>(c, it, grad, image, inj ? Gn : nullptr)
+                       : rev_pair_t<N, 4>(c, it, grad, image, inj ? Gn : nullptr);
         }
     }
     if (!c.plain && c.march) {
