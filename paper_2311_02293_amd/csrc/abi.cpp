@@ -133,11 +133,13 @@ struct smi_state {
 
 namespace {
 
-// The plan shape an autotuner pick holds for: geometry, batch, schedule and job kind.
+// The plan shape an autotuner pick holds for: geometry, batch, schedule and job kind, and whether
+// the two-step launches can run it (the receivers' rows and the size of the workspace decide).
 std::string shape_key(const Plan &pl) {
     char b[256];
-    snprintf(b, sizeof b, "%d %d %d %d %d %d %d %d %d %d %d %d", pl.nd, pl.N, pl.n[0], pl.n[1],
-             pl.n[2], pl.g.nb, pl.nshot, pl.g.nt, pl.g.box, pl.g.dr, pl.g.freesurf, (int)pl.save);
+    snprintf(b, sizeof b, "%d %d %d %d %d %d %d %d %d %d %d %d %d", pl.nd, pl.N, pl.n[0], pl.n[1],
+             pl.n[2], pl.g.nb, pl.nshot, pl.g.nt, pl.g.box, pl.g.dr, pl.g.freesurf, (int)pl.save,
+             (int)smi::steps2d_available(pl));
     return b;
 }
 
