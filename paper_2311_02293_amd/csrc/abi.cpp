@@ -449,6 +449,9 @@ smi_status check_snaps(smi_ctx *ctx, const smi_grid *g, const int *snap_it, int 
 // Forward candidates for a plan: kernel family, cells per lane, tile order, and the run width
 // and look-ahead of the fused 2D step.  Every candidate gives the default's results (bitwise
 // for the register-blocked kernels and the fused step, as the parity tests check).
+constexpr int kTuneSteps = 8;       // consecutive steps of a timing window
+static_assert(kTuneSteps % smi::kSteps == 0, "a full window holds whole two-step launches");
+
 struct Cand {
     int march;
     bool xcd, ymap, step2d;
@@ -465,7 +468,9 @@ std::vector<Cand> fwd_candidates(const Plan &pl) {
         v.push_back({2, true, false, false, 32, 2, "march2-xcd"});
         v.push_back({8, true, false, false, 32, 2, "march8-xcd"});
         v.push_back({4, false, false, false, 32, 2, "march4-plain"});
-        if (smi::steps2d_available(pl)) v.push_back({4, true, false, false, 32, 2, "two-steps", 0, 0, true});
+        // (shorter schedules have windows that a launch of two steps would run past the end of)
+        if (smi::steps2d_available(pl) && pl.nrun >= kTuneSteps)
+            v.push_back({4, true, false, false, 32, 2, "two-steps", 0, 0, true});
         if (smi::step2d_available(pl)) {
             v.push_back({4, true, false, true, 32, 2, "fused-c32-d2"});
             v.push_back({4, true, false, true, 64, 2, "fused-c64-d2"});
@@ -511,7 +516,7 @@ smi_status tune_forward(smi_ctx *ctx, const Plan &pl, const Views &w, smi::StepC
                         hipStream_t st) {
     Range range("smi autotune forward");
     const std::vector<Cand> cands = fwd_candidates(pl);
-    constexpr int K = 8;
+    constexpr int K = kTuneSteps;
     std::vector<int> steps;
     for (double f : {0.3, 0.6, 0.9}) {
         const int s0 = (int)(f * std::max(0, pl.nrun - K));

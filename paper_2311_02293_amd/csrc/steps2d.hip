@@ -584,6 +584,7 @@ hipError_t steps_t(const StepCtx &c, const Fields &src, const Fields &dst, int i
     constexpr int T = kSteps, H = 2 * N - 1, D = 2;
     const Plan &pl = *c.pl;
     const Views &w = *c.w;
+    if (!pl.side || it < 0 || it + T > pl.nrun) return hipErrorInvalidValue;   // no rows, or no boxes
     const int s0 = c.s0, s1 = shot_end(c);
     int z0 = pl.M[0], z1 = 0, ex = 0;
     for (int s = s0; s < s1; ++s) {
