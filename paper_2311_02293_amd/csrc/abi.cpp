@@ -278,9 +278,10 @@ struct Key {
 };
 
 // Everything a plan bakes into the launches of its time loop: geometry, boxes and kernel
-// choice, and the point-operator layout that decides which launches exist and how wide their
+// choice, the point-operator layout that decides which launches exist and how wide their
 // grids are (sources spread over several nodes or not, the taps per source, the nodes of the
-// adjoint-source gather).
+// adjoint-source gather), and where the workspace holds what the loop reads and writes (the rows of
+// the two-step launches are in it or not by the size that the call gives).
 Key plan_key(char tag, const Plan &pl, const smi::StepCtx &c) {
     Key k;
     k.put(tag).put(pl.geom).put(pl.band).put(pl.nshot).put(pl.nrun).put(pl.nsave);
@@ -289,6 +290,9 @@ Key plan_key(char tag, const Plan &pl, const smi::StepCtx &c) {
     k.vec(pl.fbox).vec(pl.abox).vec(pl.rbox).vec(pl.rec_off);
     k.put(pl.src_multi).vec(pl.src_toff).vec(pl.src_cell).vec(pl.inj_off);
     k.put(pl.inj_fused).put(pl.inj_zlo).put(pl.inj_nrow).put(pl.rec_zlo).put(pl.rec_nrow);
+    for (size_t o : {pl.off_model, pl.off_tables, pl.off_fields, pl.off_fields2, pl.off_side, pl.off_adj,
+                     pl.off_bands, pl.off_fin, pl.off_acc, pl.off_rho})
+        k.put(o);
     return k;
 }
 
