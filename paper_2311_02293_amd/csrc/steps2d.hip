@@ -593,6 +593,8 @@ hipError_t steps_t(const StepCtx &c, const Fields &src, const Fields &dst, int i
         z1 = std::max(z1, b[1]);
         ex = std::max(ex, b[3] - b[2]);
     }
+    // (the image rows that rows of the box read are written by lanes of their own)
+    if (pl.g.freesurf && z0 < pl.g.nb + N) z0 = std::min(z0, pl.g.nb - N);
     z0 = zalign(z0);
     const int rows = z1 - z0;
     // Strip height (64 W lanes) and run length: the least modelled time over the rounds in which
