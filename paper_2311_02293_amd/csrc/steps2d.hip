@@ -601,17 +601,17 @@ hipError_t steps_t(const StepCtx &c, const Fields &src, const Fields &dst, int i
     z0 = zalign(z0);
     const int rows = z1 - z0;
     // Strip height (64 W lanes) and run length: the least modelled time over the rounds in which
-    // the workgroups run.  A CU holds 12 wavefronts of the order-4 kernel (8 of order 8), a run of R
-    // columns takes R + 8 T iterations, and an iteration gets slower with the wavefronts that share
-    // a SIMD (about 0.3 of its time alone for each further one).
-    constexpr int kWaves = N == 2 ? 12 : 8;
+    // the workgroups run.  A CU holds 12 wavefronts of the order-4 kernel (8 of order 8) and, by its
+    // LDS, 3 workgroups (2), a run of R columns takes R + 8 T iterations, and an iteration gets
+    // slower with the wavefronts that share a SIMD (about 0.3 of its time alone for each further one).
+    constexpr int kWaves = N == 2 ? 12 : 8, kGroups = 160 * 1024 / (int)sizeof(Lds<N, T>);
     int W = kRows / 64, nstrip = 1, step = 0, R = 2 * N;
     double best = 0;
     for (int q = kRows / 64; q >= 1; --q) {
         int st = 0;
         const int n = strips_of(q, rows, T * H, st);
         if (n <= 0) continue;
-        const int cap = std::max(1, kWaves / q);        // workgroups resident on a CU
+        const int cap = std::max(1, std::min(kWaves / q, kGroups));     // workgroups resident on a CU
         for (int r = 2 * N; r <= kRun; r += r < 64 ? 2 * N : 16) {
             const long long nwg = (long long)(s1 - s0) * n * ((ex + r - 1) / r);
             const long long rounds = (nwg + 256 * cap - 1) / (256 * cap);
