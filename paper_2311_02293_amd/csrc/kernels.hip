@@ -1729,7 +1729,7 @@ hipError_t recon_march_t(const StepCtx &c, int it, bool grad, bool image) {
 // the two-launch reverse step of the 2D default path (see k_rev_pv); G: the adjoint sources
 // of level it - 1 join the second launch (k_rev_vp with INJ), or null
 template <int N, int CM>
-hipError_t rev_pair_t(const StepCtx &c, int it, bool grad, bool image, const float *G) {
+hipError_t rev_pair_t(const StepCtx &c, int it, bool grad, bool image, const float *G, bool *rho) {
     const Plan &pl = *c.pl;
     const Views &w = *c.w;
     const int *rb = w.rbox + (size_t)it * pl.nshot * 6;
@@ -1771,7 +1771,8 @@ hipError_t rev_pair_t(const StepCtx &c, int it, bool grad, bool image, const flo
     }
     RhoArg ra{};
     dim3 grid2 = grid;
-    if (c.rho) {
+    bool faces = c.rho;
+    if (faces) {
         int ez = 0, ex = 0;
         for (int s = s0; s < s1; ++s) {
             const int *b = &pl.rbox[((size_t)it * pl.nshot + s) * 6];
@@ -1780,13 +1781,16 @@ hipError_t rev_pair_t(const StepCtx &c, int it, bool grad, bool image, const flo
         }
         ra = RhoArg{w.acc_r[0], w.acc_r[1], (int)grid.z, (ez + 63) / 64, (ex + 3) / 4, s0};
         const long long per = (long long)grid.x * grid.y;
-        grid2.z += (unsigned)(((long long)ns * ra.nzb * ra.nxb + per - 1) / per);
+        const long long planes = grid.z + ((long long)ns * ra.nzb * ra.nxb + per - 1) / per;
+        faces = planes <= kMaxPlanes;       // else the caller's launch of their own
+        if (faces) grid2.z = (unsigned)planes;
     }
+    if (rho) *rho = faces;
     auto second = [&](auto fs) {
         constexpr bool F = decltype(fs)::value;
 #define SMI_RVP(I_, B_, J_)                                                                    \
     do {                                                                                       \
-        if (c.rho)                                                                             \
+        if (faces)                                                                             \
             hipLaunchKernelGGL((k_rev_vp<N, CM, I_, B_, J_, F, true>), grid2, block, 0, c.st, pl.geom, \
                                w.f, w.q, w.model, w.cpml, rb, ab, LR.mg, LA.mg, ns,             \
                                (const long long *)w.src_cell, c.stf, pl.g.nt, it, w.acc_i, ba, ia, ra); \
@@ -1822,7 +1826,6 @@ hipError_t rev_step_t(const StepCtx &c, int it, bool grad, bool image, const flo
         if (!c.plain && c.march == 4 && !c.zl && (c.rev == 1 || (c.rev == 0 && small))) {
             const bool inj = Gn && it > 0 && pl.inj_fused;
             if (fused) *fused = inj;
-            if (rho) *rho = c.rho;
             // Two cells per lane up to 0.8 M padded cells per launch, where the launch has fewer
             // than four wavefronts per SIMD and lasts as long as one of them (four cells hold
             // twice the loads of a serial lane).  Order 8, gradient of 800 steps, four -> two
@@ -1832,8 +1835,8 @@ hipError_t rev_step_t(const StepCtx &c, int it, bool grad, bool image, const flo
             // the same within 2 %.
             constexpr double kFewCells = 0.8e6;
             const bool few = (double)(se - sa) * (double)pl.P <= kFewCells;
-            return few ? rev_pair_t<N, 2>(c, it, grad, image, inj ? Gn : nullptr)
-                       : rev_pair_t<N, 4>(c, it, grad, image, inj ? Gn : nullptr);
+            return few ? rev_pair_t<N, 2>(c, it, grad, image, inj ? Gn : nullptr, rho)
+                       : rev_pair_t<N, 4>(c, it, grad, image, inj ? Gn : nullptr, rho);
         }
     }
     if (!c.plain && c.march) {
@@ -2112,7 +2115,8 @@ hipError_t born_pair_t(const StepCtx &c, int it, const float *dkappa) {
 }
 
 bool born_pair_available(const StepCtx &c) {
-    return c.pl->nd == 2 && !c.plain && c.march == 4 && !c.zl && !c.step2d;
+    return c.pl->nd == 2 && !c.plain && c.march == 4 && !c.zl && !c.step2d &&
+           2 * c.pl->nshot + 1 <= kMaxPlanes;
 }
 
 hipError_t born_pair(const StepCtx &c, int it, const float *dkappa) {

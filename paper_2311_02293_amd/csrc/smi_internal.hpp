@@ -29,6 +29,7 @@ constexpr int kTailCols = 32;  // columns of workspace slack after the last regi
 constexpr size_t kInjMapCap = size_t(1) << 22;   // entries of the largest adjoint-source node map
 constexpr double kKaiserBeta = 6.31;
 constexpr int kSteps = 2;      // time steps per launch of the pipelined 2D forward step (steps2d.hip)
+constexpr int kMaxPlanes = 65535;  // most planes (blockIdx.z) of a launch, as the plan bounds the shots
 constexpr int kSideRows = 16;  // most rows of p kept per level for receivers between its launches
 
 // ---------------------------------------------------------------- device-side views
