@@ -31,6 +31,7 @@ constexpr double kKaiserBeta = 6.31;
 constexpr int kSteps = 2;      // time steps per launch of the pipelined 2D forward step (steps2d.hip)
 constexpr int kMaxPlanes = 65535;  // most planes (blockIdx.z) of a launch, as the plan bounds the shots
 constexpr int kSideRows = 16;  // most rows of p kept per level for receivers between its launches
+constexpr int kSidePad = 16;   // columns of room after them, for what its launches store past a run
 
 // ---------------------------------------------------------------- device-side views
 
@@ -236,14 +237,14 @@ struct Views {
     float *G;           // [nt * R] adjoint source (when computed internally)
     float *dcal;        // internal dcal when the caller gave none
     float *fin;         // level-nt copy of p and v while the forward runs past nt (dr > 1)
-    float *side;        // [2][kSteps][nshot][M[1]][rec_nrow] receiver rows of two launches
+    float *side;        // [2][kSteps][nshot][M[1] + kSidePad][rec_nrow] receiver rows of two launches
 };
 
 Views views(const Plan &pl, void *ws);
 
 // bytes of the receiver rows of the pipelined 2D step (two launches)
 inline size_t side_bytes(const Plan &pl) {
-    return sizeof(float) * 2 * kSteps * (size_t)pl.nshot * pl.rec_nrow * pl.M[1];
+    return sizeof(float) * 2 * kSteps * (size_t)pl.nshot * pl.rec_nrow * (pl.M[1] + kSidePad);
 }
 // bytes of one field set (p, v and the memory variables of every shot)
 inline size_t fields_bytes(const Plan &pl) {

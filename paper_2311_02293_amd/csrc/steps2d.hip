@@ -78,7 +78,7 @@ struct SBand {
 // one receiver's sample of step it from the side rows of p after that step
 __device__ __forceinline__ void side_sample(const Geom &g, const Recv &rv, const float *side, int zlo,
                                             int nrow, float *dcal, int it, unsigned *status, int r) {
-    const float *sd = side + (long long)rv.shot[r] * nrow * g.M[1];
+    const float *sd = side + (long long)rv.shot[r] * nrow * (g.M[1] + kSidePad);
     float v = 0.f;
     for (int t = rv.toff[r]; t < rv.toff[r + 1]; ++t) {
         const int rel = (int)(rv.tcell[t] - g.org);
@@ -232,8 +232,8 @@ __device__ __forceinline__ void march(const Geom &g, const Fields &A, const Fiel
     }
     const float psgn = FS && zr <= N ? -1.f : 1.f;   // the image rows of p are odd
     const unsigned sdc = 4u * (unsigned)sg.nrow;
-    const unsigned asd = sg.aside + (unsigned)s * sdc * (unsigned)g.M[1];
-    const unsigned sdl = (unsigned)sg.nall * sdc * (unsigned)g.M[1];
+    const unsigned asd = sg.aside + (unsigned)s * sdc * (unsigned)(g.M[1] + kSidePad);
+    const unsigned sdl = (unsigned)sg.nall * sdc * (unsigned)(g.M[1] + kSidePad);
 
     float pw[T][U], vx[T][U], vz[T][U];     // rings by column
     float qz[U], uz[U];                     // memory variables of d_z p, d_z v_z on their way to the next step
@@ -406,9 +406,12 @@ __device__ __forceinline__ void march(const Geom &g, const Fields &A, const Fiel
                     const int sc = (u + 4 * U - (l + 1) * H) & M;
                     if (ACT < 2 * T && c < x0) continue;
                     const float pn = l + 1 < T ? pw[l + 1 < T ? l + 1 : 0][sc] : pt;
-                    // (the run's own columns alone: level l is (T - 1 - l) H columns ahead of the
-                    // last, and a last run rounded up to U columns would pass the end of a row)
-                    if ((ev & kEvRec) && c < x1) {
+                    if (ev & kEvRec) {
+                        // Columns past the run's own hold what the next run stores there, or zeros
+                        // past the box: a last run is rounded up to U columns, and the first level
+                        // is H columns ahead of the last.  The rows have room for them (a test of
+                        // the column costs 1 % of a small launch).
+                        static_assert((T - 1) * H + U - 1 <= kSidePad, "receiver rows too short");
                         const unsigned co = asd + l * sdl + sdc * (unsigned)c;
                         bst(rs, vsd, co, pn);
                         if (FS) bst(rs, vsm, co, -pn);
@@ -485,7 +488,7 @@ __global__ __launch_bounds__(kRows) void k_steps2d(Geom g, Fields A, Fields B, M
     constexpr int H = 2 * N - 1;
     __shared__ Lds<N, T> lds;
     const int nl = (int)blockDim.x;
-    const int sidel = sg.nall * sg.nrow * g.M[1];
+    const int sidel = sg.nall * sg.nrow * (g.M[1] + kSidePad);
     if ((int)blockIdx.x >= sg.nmain) {
         // receivers of the previous launch's levels, from its side rows
         const int nthr = ((int)gridDim.x - sg.nmain) * nl;
