@@ -250,9 +250,11 @@ __device__ __forceinline__ void march(const Geom &g, const Fields &A, const Fiel
     const int ks = x0 + T * H - 2 * T * U;          // first column
     auto colo = [&](int c) { return colb * (unsigned)((XE ? max(c, -GH) : c) + GH); };
     auto gcol = [&](int c) { return (unsigned)(XE ? min(max(c, 0), g.M[1] - 1) : c); };
-    // columns of p and v past the shot's frame read its last column, which is always zero: the next
-    // shot's field lies there, and what it holds need not be finite
-    auto colf = [&](int c) { return colo(XE ? min(c, g.M[1] + GH - 1) : c); };
+    // Columns of p and v past the shot's frame read its last column, which is always zero: the next
+    // shot's field lies there, and what it holds need not be finite.  (At order 4 what a stored
+    // column depends on, T H and at most U - 1 columns past the grid, stays within the two frames.)
+    constexpr bool kPast = T * H + U - 1 > 2 * GH;
+    auto colf = [&](int c) { return colo(XE && kPast ? min(c, g.M[1] + GH - 1) : c); };
     auto load = [&](int k, Ld &L) __attribute__((always_inline)) {
         L.p = bld(rs, vr, ap + colf(k));
         const unsigned cv = colf(k - N);
