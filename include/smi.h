@@ -107,7 +107,8 @@ typedef enum {
                                 and of sources off the grid run two steps per launch (same
                                 results; not with snapshots or
                                 SMI_OPT_TIMING, nor with receivers whose nodes span
-                                more than 16 rows); in 3D the forward and adjoint
+                                more than 16 rows, and where bands are saved only where that
+                                is faster); in 3D the forward and adjoint
                                 half steps of 5 (marching along y, SMI_OPT_CHUNK 0) where
                                 they apply, register-blocked kernels with 2 cells per lane
                                 elsewhere;

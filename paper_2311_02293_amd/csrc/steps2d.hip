@@ -688,7 +688,9 @@ hipError_t steps_t(const StepCtx &c, const Fields &src, const Fields &dst, int i
     const std::true_type yes{};
     const std::false_type no{};
     if (pl.g.freesurf) return pl.save ? launch(yes, yes) : launch(yes, no);
-    return pl.save ? launch(no, yes) : launch(no, no);
+    if constexpr (N == 2)
+        if (pl.save) return launch(no, yes);
+    return pl.save ? hipErrorInvalidValue : launch(no, no);     // (see steps2d_available)
 }
 
 // receivers of the levels of one launch (first step it) from its side rows
@@ -707,15 +709,32 @@ bool steps2d_available(const Plan &pl) {
     if (pl.nd != 2 || !pl.dbuf || !pl.side) return false;
     // with a free surface a lane holds at most one row of the saved z faces
     if (pl.g.freesurf && pl.n[0] <= pl.N + 1) return false;
+    // order 8 saving bands without a free surface: slower throughout (see below), not compiled
+    if (pl.N == 4 && pl.save && !pl.g.freesurf) return false;
     // 31-bit byte offsets from the model over both field sets and the receiver rows
     return pl.off_side + side_bytes(pl) - pl.off_model < (size_t(1) << 31) - (1u << 20);
 }
 
-// Order 4 always (0.66 to 0.79 of the half-step kernels' time without saved bands, 0.94 to 0.99 of
-// a whole gradient with them); order 8 where some source spreads over several nodes, whose
-// injection and images cost the half-step kernels two launches per step more (0.59 to 0.82, and
-// 0.81 to 0.85 of a whole gradient), and not otherwise (0.86 to 1.29).
-bool steps2d_default(const Plan &pl) { return steps2d_available(pl) && (pl.N == 2 || pl.src_multi); }
+// Where they are the default.  Time of a forward pass against the half-step kernels' (two cells per
+// lane where those are small): geometric mean and range over 40 x 40 to 500 x 1500 cells, 1 to 32
+// shots, boxes on and off.  A source that spreads over several nodes costs the half-step kernels a
+// launch per step, two below a free surface; saving bands takes the marching loop's wavefronts at the
+// faces off their main path and spills its scalar registers.
+//   without saved bands: order 4 0.81 (0.61-0.95), below a free surface 0.87 (0.65-1.02), spread
+//     sources 0.65 (0.54-0.83), both 0.51 (0.39-0.74); order 8 with spread sources below a free
+//     surface 0.92 (0.75-1.10), without one 0.98 (0.78-1.16), but 1.21 (1.08-1.29) on less than
+//     32768 padded cells per shot; order 8 with sources on the grid 0.86 to 1.29
+//   with them: order 4 1.01 (0.75-1.21), every fifth level 0.95 (0.69-1.10), spread sources 0.77
+//     (0.61-1.07), also below a free surface 0.72 (0.54-1.45), there with sources on the grid 1.23
+//     (0.87-1.90); order 8 with spread sources 1.31 (1.03-1.62), every fifth level 1.17
+//     (0.91-1.46), below a free surface 1.06 (0.93-1.48), every fifth level there 0.99 (0.87-1.32)
+bool steps2d_default(const Plan &pl) {
+    if (!steps2d_available(pl)) return false;
+    if (pl.N == 2) return !pl.save || pl.src_multi || !pl.g.freesurf;
+    if (!pl.src_multi) return false;
+    if (pl.g.freesurf) return !pl.save || pl.g.dr > 1;
+    return (long long)pl.M[0] * pl.M[1] >= 32768;
+}
 
 hipError_t fwd_steps_2d(const StepCtx &c, const Fields &src, const Fields &dst, int it, int par) {
     return c.pl->N == 2 ? steps_t<2>(c, src, dst, it, par) : steps_t<4>(c, src, dst, it, par);
