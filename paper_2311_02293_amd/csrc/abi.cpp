@@ -651,7 +651,7 @@ smi_status run_forward(smi_ctx *ctx, const Plan &pl, const Views &w, const float
     // in the last-level cache between the launches of a step (one group when all of them fit);
     // every shot's arithmetic is the one of a single loop
     const std::vector<int> fg = pl.nd == 2 && !c.plain && !fused && c.march > 0
-                                    ? smi::fwd_groups(pl, kGroupBudget, ctx->opt_fwd_group)
+                                    ? smi::fwd_groups(pl, kGroupBudget, ctx->opt_fwd_group, c.steps)
                                     : std::vector<int>{0, pl.nshot};
     // level nt of (p, v) of the current group: from src into dst (same layout, every shot)
     auto copy_state = [&](float *dst, const float *src, hipStream_t ls) -> hipError_t {

@@ -198,7 +198,7 @@ void step_bytes_of(const Plan &pl, int it, int s0, int s1, double row[3]);
 // shot groups of a 2D forward pass of the register-blocked kernels: one group while every
 // step's fields (with their memory variables) fit `budget` bytes, else the group count of least
 // modelled cost over the schedule of boxes; max_per > 0 caps a group instead
-std::vector<int> fwd_groups(const Plan &pl, double budget, int max_per);
+std::vector<int> fwd_groups(const Plan &pl, double budget, int max_per, bool steps);
 // algorithmic bytes of reverse iteration it over the shots [s0, s1): out[0] the adjoint and
 // reconstruction steps with band restores, adjoint sources and the model read once, out[1] the
 // gradient sum, out[2] the image sum, out[3] the illumination sum
