@@ -315,12 +315,12 @@ std::vector<int> fwd_groups(const Plan &pl, double budget, int max_per, bool ste
     const int ns = pl.nshot, nrun = pl.nrun;
     if (pl.nd != 2 || ns <= 1) return {0, ns};
     if (max_per > 0) return equal_groups(ns, std::min(ns, max_per));
-    // The two-step launches of order 8 are bound by instruction issue, not by what they read, and
-    // fill the chip better with more shots: one loop.  (Boxes off, per 200 steps: 500 x 1500, 32
-    // shots 36.6 ms in groups of 16, 29.8 in one loop; 1000 x 1000, 24 shots 32.3 and 27.5, below a
-    // free surface 38.4 and 32.2.)  At order 4 the groups of the model below are within 1 % of the
-    // best of forced sizes with boxes on, within 12 % with boxes off (500 x 1500, 16 shots, per 300
-    // steps: 18.9 ms in one loop, 16.8 in groups of 8).
+    // The two-step launches of order 8 are held back by their few wavefronts, not by what the
+    // last-level cache misses, and fill the chip better with more shots: one loop.  (Boxes off, per
+    // 200 steps: 500 x 1500, 32 shots 36.6 ms in groups of 16, 29.8 in one loop; 1000 x 1000, 24 shots
+    // 32.3 and 27.5, below a free surface 38.4 and 32.2.)  At order 4 the groups of the model below
+    // are within 1 % of the best of forced sizes with boxes on, within 12 % with boxes off (500 x
+    // 1500, 16 shots, per 300 steps: 18.9 ms in one loop, 16.8 in groups of 8).
     if (steps && pl.N == 4) return {0, ns};
     // bytes of the fields and memory variables over `cells` box cells (the model is shared)
     auto bytes = [&](double cells) {

@@ -18,18 +18,22 @@
 // Each cell's arithmetic is the one of the half-step kernels, so both give the same fields
 // bitwise.
 //
-// What bounds it: the instructions a SIMD can issue, with the two or three wavefronts per SIMD
-// that the rings leave room for (131 vector registers at order 4, about 200 at order 8: 73
-// vector and 34 scalar instructions per 64 cells and two steps on the main path at order 8).  It
-// saves launches (one per two steps instead of four, and instead of the source and free-surface
-// launches beside them), which is what small grids and spread sources pay for, and half of the
-// fields' traffic.  Against the half-step kernels, 1000 steps: order 4, 500 x 1500, 1 / 4 / 16
-// shots 8.70 / 11.5 / 25.6 -> 6.69 / 9.07 / 16.9 ms, 800 x 2000, 8 shots, box off 92.6 -> 68.3 ms;
-// order 8 with off-grid sources, 500 x 1500, 16 shots 227 -> 185 ms, 263 x 611 below a free
-// surface, 6 shots 59.4 -> 34.9 ms; order 8 on the grid it is between 0.86 and 1.29 of their time
-// (500 x 1500 x 16 shots 258 -> 265 ms per 4000 steps, 150 x 200 x 1 shot 9.1 -> 11.7 ms), so
-// there the half-step kernels stay the default.  Loads 4 columns ahead instead of 2, one step per
-// launch instead of two, and three wavefronts per SIMD at order 8 (by spilling) measured slower.
+// What bounds it: the two or three wavefronts per SIMD that the rings leave room for (131 vector
+// registers at order 4, about 200 at order 8).  Counted on 500 x 1500, 32 shots, boxes off: 1.6 to
+// 1.8 of them resident per SIMD, an instruction in flight in 71 % of a SIMD's cycles at order 8 (48 % at
+// order 4), 4.4 TB/s (4.3) of the 6.2 that a copy reaches; at order 8 62 vector instructions per cell
+// and step, 37 of them on the main path of a cell, the others for halos, slabs and edges.
+// Small grids wait for the serial chain of one march.  It saves launches
+// (one per two steps instead of four, and instead of the source and free-surface launches beside
+// them), which is what small grids and spread sources pay for, and half of the fields' traffic.
+// Against the half-step kernels, 1000 steps: order 4, 500 x 1500, 1 / 4 / 16 shots 7.77 / 10.8 / 21.4
+// -> 6.64 / 8.38 / 13.0 ms, 800 x 2000, 8 shots, box off 90.1 -> 66.0 ms; order 8 with off-grid
+// sources, 263 x 611 below a free surface, 6 shots 19.2 -> 16.6 ms, and 4000 steps of 300 x 900,
+// 16 shots 165 -> 135, 500 x 1500, 16 / 32 shots 254 / 511 -> 262 / 449 ms; order 8 on the grid it is
+// between 0.86 and 1.29 of their time (500 x 1500 x 16 shots 258 -> 265 ms per 4000 steps,
+// 150 x 200 x 1 shot 9.1 -> 11.7 ms), so there the half-step kernels stay the default.  Loads 4
+// columns ahead instead of 2, one step per launch instead of two, and three wavefronts per SIMD at
+// order 8 (by spilling) measured slower.
 #include <algorithm>
 #include <type_traits>
 
