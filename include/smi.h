@@ -138,8 +138,9 @@ typedef enum {
                                 and 8 give way to the kernels of 0 (the y-marching kernels of 0
                                 and 5 write the image rows themselves). */
     SMI_OPT_GRAPH = 1,       /* 1: the time loops of a call run as a HIP graph, captured the
-                                first time a plan is seen (same geometry, boxes, kernels and
-                                buffers) and replayed on later calls; up to 8 graphs are kept
+                                first time a plan is seen (same geometry, boxes, kernels,
+                                buffers and workspace layout, which in 2D depends on the size
+                                given) and replayed on later calls; up to 8 graphs are kept
                                 per context (default 0).  Not combined with SMI_OPT_TIMING. */
     SMI_OPT_CHUNK = 2,       /* tuning.  SMI_OPT_KERNEL 3: cells per lane (2, 4, 8; else 4),
                                 plus 100 to take the z-neighbours from LDS.
@@ -171,7 +172,9 @@ typedef enum {
                                 hold up to 8 M padded cells, five launches above; 1 always two;
                                 2 always five.  Same results. */
     SMI_OPT_AUTOTUNE = 7,    /* 1: the library picks the kernels per plan shape (geometry, shots,
-                                nt, box, dr, job kind) by timing them on the device: the first
+                                nt, box, dr, job kind, and whether the receivers and the
+                                workspace allow two 2D steps per launch) by timing them on the
+                                device: the first
                                 forward pass of a shape times every forward candidate (kernel
                                 family, cells per lane, tile order, the fused 2D step's run width
                                 and look-ahead) on 24 steps spread over the schedule, on cleared

@@ -713,7 +713,8 @@ bool steps2d_available(const Plan &pl) {
     if (pl.nd != 2 || !pl.dbuf || !pl.side) return false;
     // with a free surface a lane holds at most one row of the saved z faces
     if (pl.g.freesurf && pl.n[0] <= pl.N + 1) return false;
-    // order 8 saving bands without a free surface: slower throughout (see below), not compiled
+    // order 8 saving bands without a free surface: the slower one nearly everywhere (see below), not
+    // compiled
     if (pl.N == 4 && pl.save && !pl.g.freesurf) return false;
     // 31-bit byte offsets from the model over both field sets and the receiver rows
     return pl.off_side + side_bytes(pl) - pl.off_model < (size_t(1) << 31) - (1u << 20);
